@@ -197,8 +197,10 @@ constexpr int kRowTile = 1024;
 // workgroups.
 constexpr int64_t kPoolRowMinGroups = 192;
 
+constexpr int kPoolRowThreads = 512;
+
 template <typename T>
-__global__ __launch_bounds__(512) void pool_row_kernel(const T* __restrict__ H,
+__global__ __launch_bounds__(kPoolRowThreads) void pool_row_kernel(const T* __restrict__ H,
                                                        const float* __restrict__ sp, int np,
                                                        float* __restrict__ s_out,
                                                        float* __restrict__ S, T* __restrict__ St,
@@ -1495,13 +1497,17 @@ hipError_t pool_fwd_t(const void* H, const float* sp, int np, float* s_out, floa
                       hipStream_t s) {
   const int nb = (T + L - 1) / L;
   if ((int64_t)B * nb >= kPoolRowMinGroups) {
-    // whole rows: VR vectors per row, TG token groups, VR * TG threads a
-    // multiple of 64 and at least 256 (or VR itself when larger)
+    // whole rows: VR vectors per row, TG token groups, VR * TG threads at
+    // least 256 (or VR itself when larger) and a multiple of 64 if that
+    // fits 512 threads; otherwise the last wave is partly idle
     const int VR = D / Vec16<E>::N;
-    int TG = VR >= 256 ? 1 : (256 + VR - 1) / VR;
-    while ((VR * TG) % 64) ++TG;
+    const int least = VR >= 256 ? 1 : (256 + VR - 1) / VR;
+    int TG = least;
+    while ((VR * TG) % 64 && VR * TG <= kPoolRowThreads) ++TG;
+    if (VR * TG > kPoolRowThreads) TG = least;
+    const int threads = (VR * TG + 63) / 64 * 64;
     const size_t lds = ((size_t)TG * D + kRowTile) * sizeof(float);
-    hipLaunchKernelGGL(pool_row_kernel<E>, dim3(nb, B), dim3(VR * TG), lds, s, (const E*)H, sp, np,
+    hipLaunchKernelGGL(pool_row_kernel<E>, dim3(nb, B), dim3(threads), lds, s, (const E*)H, sp, np,
                        s_out, S, (E*)St, stats, T, D, L, nb, TG, zero, nzero);
     return hipGetLastError();
   }

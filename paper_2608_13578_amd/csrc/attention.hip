@@ -1254,6 +1254,12 @@ __global__ __launch_bounds__(NW * 64, NW >= 8 ? 1 : 2) void attn_bwd_block_bf16_
       ls_s[tl] = ok ? lse[lrow + t] : 0.f;
     }
   }
+  // The tile's rows past this workgroup's queries (one wave: 32 of 64) are
+  // masked to zero probability, but 0 * (dP - delta) needs a finite delta.
+  if (NW * 32 < NT * 64 && threadIdx.x < NT * 64 - NW * 32) {
+    dl_s[NW * 32 + threadIdx.x] = 0.f;
+    ls_s[NW * 32 + threadIdx.x] = 0.f;
+  }
   vm_wait<0>();
   __syncthreads();
 

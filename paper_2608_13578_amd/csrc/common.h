@@ -250,6 +250,19 @@ __device__ __forceinline__ bf16x8 lds_read_b128(const bf16* p) {
   asm volatile("ds_read_b128 %0, %1" : "=v"(v) : "v"(a));
   return v;
 }
+// The same reads at a byte address plus an immediate offset.
+template <int OFF>
+__device__ __forceinline__ bf16x4 lds_read_tr_at(unsigned a) {
+  s16x4 v;
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(a), "n"(OFF));
+  return __builtin_bit_cast(bf16x4, v);
+}
+template <int OFF>
+__device__ __forceinline__ bf16x8 lds_read_b128_at(unsigned a) {
+  bf16x8 v;
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(a), "n"(OFF));
+  return v;
+}
 // Waits for every outstanding LDS read of this wave.
 __device__ __forceinline__ void lds_tr_wait() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 // Waits until at most N of this wave's LDS reads are outstanding (they

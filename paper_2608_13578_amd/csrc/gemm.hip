@@ -19,6 +19,8 @@
 // a lane ends up holding four consecutive output columns of one output row:
 // the epilogue stores 8 (bf16) or 16 (f32) contiguous bytes per lane.
 #include <algorithm>
+#include <type_traits>
+#include <utility>
 
 #include "common.h"
 #include "kernels.h"
@@ -272,28 +274,67 @@ __device__ __forceinline__ void staged_epilogue(const Epi& epi, const f32x4 (&ac
 
 // ------------------------------------------------------------------ epilogues
 
+// 8 consecutive elements as loaded, converted when used.
+template <typename T> struct Raw8;
+template <> struct Raw8<bf16> {
+  bf16x8 v;
+  __device__ __forceinline__ void load(const bf16* p) { v = *reinterpret_cast<const bf16x8*>(p); }
+  __device__ __forceinline__ float at(int e) const { return (float)v[e]; }
+};
+template <> struct Raw8<float> {
+  f32x4 v[2];
+  __device__ __forceinline__ void load(const float* p) {
+    v[0] = *reinterpret_cast<const f32x4*>(p);
+    v[1] = *reinterpret_cast<const f32x4*>(p + 4);
+  }
+  __device__ __forceinline__ float at(int e) const { return v[e >> 2][e & 3]; }
+};
+
+// What an epilogue reads from memory for 8 columns: pre() requests it and
+// fin8() uses it, so that a caller can keep the requests of several items
+// in flight ahead of the stores of others.
+template <class Epi, class = void>
+struct HasPre {
+  static constexpr bool value = false;
+};
+template <class Epi>
+struct HasPre<Epi, std::void_t<typename Epi::Pre>> {
+  static constexpr bool value = true;
+};
+
 template <typename TO, typename TA>
 struct EpiStore {
   TO* C;
   int64_t ldc;
   const TA* add;
   int64_t ld_add;
+  struct Pre {
+    Raw8<TA> a;
+  };
+  __device__ __forceinline__ void pre(int m, int n, bool ok, Pre& p) const {
+    if (add && ok) p.a.load(add + (int64_t)m * ld_add + n);
+  }
+  __device__ __forceinline__ void fin8(int m, int n, const float (&v)[8], bool ok,
+                                       const Pre& p) const {
+    if (!ok) return;
+    TO* c = C + (int64_t)m * ldc + n;
+    if (!add) {
+      st8(c, v);
+      return;
+    }
+    float o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = v[e] + p.a.at(e);
+    st8(c, o);
+  }
   __device__ __forceinline__ void operator()(int m, int n, f32x4 v) const {
     if (add) v += load4f(add + (int64_t)m * ld_add + n);
     store4(C + (int64_t)m * ldc + n, v[0], v[1], v[2], v[3]);
   }
   __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
-    if (!ok) return;
-    float o[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = v[e];
-    if (add) {
-      float a[8];
-      ld8(add + (int64_t)m * ld_add + n, a);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) o[e] += a[e];
-    }
-    st8(C + (int64_t)m * ldc + n, o);
+    Pre p;
+    pre(m, n, ok, p);
+    fin8(m, n, v, ok, p);
   }
 };
 
@@ -346,6 +387,20 @@ struct EpiGeluBwd {
   const T* U;
   T* dU;
   int64_t ld;
+  struct Pre {
+    Raw8<T> u;
+  };
+  __device__ __forceinline__ void pre(int m, int n, bool ok, Pre& p) const {
+    if (ok) p.u.load(U + (int64_t)m * ld + n);
+  }
+  __device__ __forceinline__ void fin8(int m, int n, const float (&v)[8], bool ok,
+                                       const Pre& p) const {
+    if (!ok) return;
+    float d[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) d[k] = v[k] * gelu_grad_f(p.u.at(k));
+    st8(dU + (int64_t)m * ld + n, d);
+  }
   __device__ __forceinline__ void operator()(int m, int n, f32x4 v) const {
     const int64_t off = (int64_t)m * ld + n;
     const f32x4 u = load4f(U + off);
@@ -354,13 +409,9 @@ struct EpiGeluBwd {
     store4(dU + off, v[0], v[1], v[2], v[3]);
   }
   __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
-    if (!ok) return;
-    const int64_t off = (int64_t)m * ld + n;
-    float u[8], d[8];
-    ld8(U + off, u);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) d[k] = v[k] * gelu_grad_f(u[k]);
-    st8(dU + off, d);
+    Pre p;
+    pre(m, n, ok, p);
+    fin8(m, n, v, ok, p);
   }
 };
 
@@ -491,35 +542,43 @@ struct EpiGate {
     store4(reinterpret_cast<T*>(e.Y) + off, y[0], y[1], y[2], y[3]);
     store4(reinterpret_cast<typename GateT<T>::type*>(e.G) + off, g[0], g[1], g[2], g[3]);
   }
-  __device__ __forceinline__ void apply8(int m, int n, const float (&u)[8], bool ok) const {
+  struct Pre {
+    Raw8<T> h, x;
+    Raw8<float> c;
+  };
+  __device__ __forceinline__ void pre(int m, int n, bool ok, Pre& p) const {
     if (!ok) return;
     const int b = m / e.T;
-    const int t = m - b * e.T;
-    const int blk = t / e.L;
+    const int blk = (m - b * e.T) / e.L;
     const int64_t off = (int64_t)m * e.D + n;
-    float h[8], c[8], g[8], y[8];
-    ld8(reinterpret_cast<const T*>(e.H) + off, h);
+    p.h.load(reinterpret_cast<const T*>(e.H) + off);
+    if (e.X) p.x.load(reinterpret_cast<const T*>(e.X) + off);
     if (blk > 0) {
-      ld8(e.P + (int64_t)(b * e.nb + blk - 1) * e.D + n, c);
+      p.c.load(e.P + (int64_t)(b * e.nb + blk - 1) * e.D + n);
     } else if (e.Pc) {
-      ld8(e.Pc + (int64_t)b * e.D + n, c);
+      p.c.load(e.Pc + (int64_t)b * e.D + n);
     } else {
-#pragma unroll
-      for (int k = 0; k < 8; ++k) c[k] = 0.f;
+      p.c.v[0] = p.c.v[1] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    if (e.X) {
-      float x[8];
-      ld8(reinterpret_cast<const T*>(e.X) + off, x);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) h[k] += x[k];
-    }
+  }
+  __device__ __forceinline__ void fin8(int m, int n, const float (&u)[8], bool ok,
+                                       const Pre& p) const {
+    if (!ok) return;
+    const int64_t off = (int64_t)m * e.D + n;
+    float g[8], y[8];
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       g[k] = sigmoidf_(u[k]);
-      y[k] = h[k] + g[k] * c[k];
+      const float h = e.X ? p.h.at(k) + p.x.at(k) : p.h.at(k);
+      y[k] = h + g[k] * p.c.at(k);
     }
     st8(reinterpret_cast<T*>(e.Y) + off, y);
     st8(reinterpret_cast<typename GateT<T>::type*>(e.G) + off, g);
+  }
+  __device__ __forceinline__ void apply8(int m, int n, const float (&u)[8], bool ok) const {
+    Pre p;
+    pre(m, n, ok, p);
+    fin8(m, n, u, ok, p);
   }
 };
 
@@ -540,20 +599,33 @@ struct EpiHbar {
     for (int r = 0; r < 4; ++r) o[r] = v[r] + dy[r] + a * dS[r] + ds * w[r];
     store4(reinterpret_cast<T*>(e.dH) + off, o[0], o[1], o[2], o[3]);
   }
-  __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
+  struct Pre {
+    Raw8<T> dy, w;
+    Raw8<float> dS;
+    float a, ds;
+  };
+  __device__ __forceinline__ void pre(int m, int n, bool ok, Pre& p) const {
     if (!ok) return;
     const int b = m / e.T;
-    const int t = m - b * e.T;
-    const int blk = t / e.L;
-    const int64_t off = (int64_t)m * e.D + n;
-    float dy[8], dS[8], w[8], o[8];
-    ld8(reinterpret_cast<const T*>(e.dY) + off, dy);
-    ld8(e.dS + (int64_t)(b * e.nb + blk) * e.D + n, dS);
-    ld8(reinterpret_cast<const T*>(e.wp) + n, w);
-    const float a = e.a[m], ds = e.ds[m];
+    const int blk = (m - b * e.T) / e.L;
+    p.dy.load(reinterpret_cast<const T*>(e.dY) + (int64_t)m * e.D + n);
+    p.dS.load(e.dS + (int64_t)(b * e.nb + blk) * e.D + n);
+    p.w.load(reinterpret_cast<const T*>(e.wp) + n);
+    p.a = e.a[m];
+    p.ds = e.ds[m];
+  }
+  __device__ __forceinline__ void fin8(int m, int n, const float (&v)[8], bool ok,
+                                       const Pre& p) const {
+    if (!ok) return;
+    float o[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) o[k] = v[k] + dy[k] + a * dS[k] + ds * w[k];
-    st8(reinterpret_cast<T*>(e.dH) + off, o);
+    for (int k = 0; k < 8; ++k) o[k] = v[k] + p.dy.at(k) + p.a * p.dS.at(k) + p.ds * p.w.at(k);
+    st8(reinterpret_cast<T*>(e.dH) + (int64_t)m * e.D + n, o);
+  }
+  __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
+    Pre p;
+    pre(m, n, ok, p);
+    fin8(m, n, v, ok, p);
   }
 };
 
@@ -675,6 +747,19 @@ struct PipeLoad {
                                                voff[i], 0, 0, 0);
 #endif
   }
+
+#if defined(__HIP_DEVICE_COMPILE__)
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const bf16* base, bool on) const {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, on ? (int)extent : 0,
+                                             0x00020000);
+  }
+  // The i-th of this wave's loads of one slab.
+  template <int I>
+  __device__ __forceinline__ void issue_one(__amdgpu_buffer_rsrc_t rs, bf16* dst, int wave) const {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + (wave * PER + I) * 512), 16,
+                                             voff[I], 0, 0, 0);
+  }
+#endif
 
   // Fragment for rows/columns base .. base+15 of the tile, 32-wide K step ks.
   __device__ __forceinline__ static bf16x8 frag(const bf16* s, int base, int ks, int lane) {
@@ -889,6 +974,299 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
                                                       n0, wm, wn, M, N, tid);
 }
 
+// ------------------------------------------------------------------ wide kernel
+// 256 x 256 tiles for large bf16 products: four waves of 128 x 128, one per
+// SIMD, K in 64-deep slabs through two LDS stages (128 KB, one workgroup per
+// CU).  What bounds the 128 x 128 kernel above is the LDS port: per 64-deep
+// slab a CU spends 515 cycles of matrix work against 768-1024 cycles of
+// fragment reads and direct-load writes (128 B per cycle).  Here a slab is
+// 2060 cycles of matrix work against 1536 of LDS.
+//
+// With one wave per SIMD nothing else hides a wait, so every LDS read and
+// every global load is issued between matrix instructions, a fixed number
+// apart: the reads of a 32-deep step during the step before it, the loads of
+// slab kt + 2 from the barrier on that frees slab kt's stage (late in its
+// first step, when all its fragments have been read).  That barrier also
+// publishes slab kt + 1, whose loads had a whole slab's time to land.
+template <int... I, class F>
+__device__ __forceinline__ void unrolled_impl(std::integer_sequence<int, I...>, F&& f) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void unrolled(F&& f) {
+  unrolled_impl(std::make_integer_sequence<int, N>{}, f);
+}
+
+// Per-lane LDS byte addresses of a wave's 128 rows (columns) of one operand
+// in stage 0; stage 1 is 32 KB higher (bit 15).
+template <bool RCONTIG>
+struct WideFrag {
+  static constexpr int NA = RCONTIG ? 8 : 2;
+  static constexpr int READS = RCONTIG ? 16 : 8;  // LDS reads per 32-deep step
+  unsigned a[NA];
+  typedef PipeOperand<256, 64, RCONTIG> Op;
+
+  __device__ __forceinline__ void setup(unsigned base, int w0, int lane) {
+    const int lr = lane & 15, lg = lane >> 4;
+    if constexpr (!RCONTIG) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+        a[ks] = base + (w0 + lr) * 128 + ((ks * 4 + lg) ^ Op::kswz(lr)) * 16;
+    } else {
+      const int kr = lg * 8 + (lr >> 2);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        a[i] = base + kr * 512 + ((w0 / 8 + 2 * i + ((lr & 3) >> 1)) ^ Op::rswz(kr)) * 16 +
+               (lr & 1) * 8;
+    }
+  }
+  __device__ __forceinline__ void flip() {
+#pragma unroll
+    for (int i = 0; i < NA; ++i) a[i] ^= 32768u;
+  }
+  // The R-th read of 32-deep step KS: fragment R (K-contiguous), or half
+  // R % 2 of fragment R / 2.
+  template <int KS, int R>
+  __device__ __forceinline__ void read(bf16x8 (&f)[8]) const {
+    if constexpr (!RCONTIG) {
+      f[R] = lds_read_b128_at<R * 2048>(a[KS]);
+    } else {
+      bf16x4 h = lds_read_tr_at<KS * 16384 + (R & 1) * 2048>(a[R / 2]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[R / 2][(R & 1) * 4 + e] = h[e];
+    }
+  }
+};
+
+template <bool A_MC, bool B_NC, int BSEG, class Epi>
+__global__ __launch_bounds__(256, 1) void gemm_wide_kernel(int M, int N, int K,
+                                                           Operand<bf16, A_MC, kSegNone> A,
+                                                           Operand<bf16, B_NC, BSEG> B, int kchunk,
+                                                           int group, Epi epi0) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  constexpr int BK = 64;
+  typedef PipeLoad<256, BK, A_MC, 4> LA;
+  typedef PipeLoad<256, BK, B_NC, 4> LB;
+  constexpr int kStage = 256 * BK;  // elements of one operand's stage
+  // A stage 0, A stage 1, B stage 0, B stage 1
+  __shared__ __attribute__((aligned(1024))) bf16 lds[4 * kStage];
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  int tm, tn, z;
+  xcd_tile_order(group, tm, tn, z);
+  const int m0 = tm * 256, n0 = tn * 256;
+  const int kbeg = z * kchunk;
+  Epi epi = epi0;
+  bind_split(epi, z);
+  const int kend = min(K, kbeg + kchunk);
+  const int nk = kend > kbeg ? (kend - kbeg) / BK : 0;
+
+  const bf16* bptr = B.p[0];
+  int bn0 = n0, bnmax = N;
+  if constexpr (BSEG == kSegN) {
+    const int sg = n0 / B.seg_len;
+    bptr = B.p[sg];
+    bn0 = n0 - sg * B.seg_len;
+    bnmax = B.seg_len;
+  }
+  LA la;
+  LB lb;
+  la.setup(m0, M, A.ld, wave, lane);
+  lb.setup(bn0, bnmax, B.ld, wave, lane);
+  auto bslab = [&](int k) {
+    if constexpr (BSEG == kSegK) {
+      // compares, not an indexed read of the kernel's arguments: a scalar
+      // load would have to be waited for once per slab
+      const int sl = B.seg_len;
+      const bf16* p = k < sl ? B.p[0] : k < 2 * sl ? B.p[1] : B.p[2];
+      return lb.slab(p, B.ld, k < sl ? k : k < 2 * sl ? k - sl : k - 2 * sl);
+    } else {
+      return lb.slab(bptr, B.ld, k);
+    }
+  };
+  WideFrag<A_MC> ra;
+  WideFrag<B_NC> rb;
+  const unsigned lds0 = (unsigned)(uintptr_t)((lds_void_t*)lds);
+  ra.setup(lds0, wm * 128, lane);
+  rb.setup(lds0 + 2 * kStage * 2, wn * 128, lane);
+
+  f32x4 acc[8][8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 fa[2][8], fb[2][8];
+
+  constexpr int NRD = WideFrag<A_MC>::READS + WideFrag<B_NC>::READS;
+  constexpr int kBar = 52;      // matrix instruction of step 0 after which the barrier stands
+  constexpr int kReadSpan = 48; // the reads of a step are spread over this many instructions
+  // One read of step KS into fragment set SET (A's fragments first).
+  auto read1 = [&](auto rr, auto ks, auto set) {
+    constexpr int R = decltype(rr)::value, KS = decltype(ks)::value, SET = decltype(set)::value;
+    if constexpr (R < WideFrag<A_MC>::READS) ra.template read<KS, R>(fa[SET]);
+    else rb.template read<KS, R - WideFrag<A_MC>::READS>(fb[SET]);
+  };
+  // The 16 loads of a slab, one at a time (A's first).
+  auto load1 = [&](auto uu, __amdgpu_buffer_rsrc_t rsa, __amdgpu_buffer_rsrc_t rsb, bf16* sa) {
+    constexpr int U = decltype(uu)::value;
+    if constexpr (U < LA::PER) la.template issue_one<U>(rsa, sa, wave);
+    else lb.template issue_one<U - LA::PER>(rsb, sa + 2 * kStage, wave);
+  };
+  constexpr int NLD = LA::PER + LB::PER;
+  constexpr std::integral_constant<int, 0> c0{};
+  constexpr std::integral_constant<int, 1> c1{};
+
+  // One slab; `la` and `lb` load slab kt + 2 (nothing when there is none: a
+  // descriptor of no extent).  The code is one copy on purpose: it runs from
+  // a cold instruction cache, and copies without the loads and the reads for
+  // the last two slabs cost a short product more than the work they skip.
+  auto slab = [&](int kt) {
+    const bool load = kt + 2 < nk;
+    const int k = kbeg + (load ? kt + 2 : kt) * BK;
+    const __amdgpu_buffer_rsrc_t rsa = la.rsrc(la.slab(A.p[0], A.ld, k), load);
+    const __amdgpu_buffer_rsrc_t rsb = lb.rsrc(bslab(k), load);
+    bf16* sa = lds + (kt & 1) * kStage;
+    asm volatile("s_nop 2");
+    unrolled<64>([&](auto ix) {
+      constexpr int x = decltype(ix)::value;
+      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                   : "+a"(acc[x >> 3][x & 7])
+                   : "v"(fb[0][x & 7]), "v"(fa[0][x >> 3]));
+      constexpr int r0 = x * NRD / kReadSpan, r1 = (x + 1) * NRD / kReadSpan;
+      if constexpr (x < kReadSpan && r1 > r0) read1(std::integral_constant<int, r0>{}, c1, c1);
+      if constexpr (x == kBar) {
+        // this wave has read all of slab kt, and its loads of slab kt + 1
+        // have landed; after the barrier both hold for every wave
+        lds_wait<0>();
+        wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+      }
+      if constexpr (x > kBar && (x & 3) == 3)
+        load1(std::integral_constant<int, (x - kBar - 3) / 4>{}, rsa, rsb, sa);
+    });
+    ra.flip();
+    rb.flip();
+    asm volatile("s_nop 2");
+    constexpr int U0 = (64 - kBar) / 4;  // loads issued so far
+    unrolled<64>([&](auto ix) {
+      constexpr int x = decltype(ix)::value;
+      asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0"
+                   : "+a"(acc[x >> 3][x & 7])
+                   : "v"(fb[1][x & 7]), "v"(fa[1][x >> 3]));
+      constexpr int r0 = x * NRD / kReadSpan, r1 = (x + 1) * NRD / kReadSpan;
+      if constexpr (x < kReadSpan && r1 > r0) read1(std::integral_constant<int, r0>{}, c0, c0);
+      if constexpr ((x & 3) == 3 && U0 + (x >> 2) < NLD)
+        load1(std::integral_constant<int, U0 + (x >> 2)>{}, rsa, rsb, sa);
+    });
+    lds_wait<0>();
+  };
+
+  // Prologue: both stages receive their slabs (a lone slab twice).
+#pragma unroll
+  for (int st = 0; st < 2; ++st) {
+    const int k = kbeg + min(st, nk - 1) * BK;
+    la.issue(la.slab(A.p[0], A.ld, k), lds + st * kStage, wave);
+    lb.issue(bslab(k), lds + (2 + st) * kStage, wave);
+  }
+  wait_vmcnt<NLD>();
+  __builtin_amdgcn_s_barrier();
+  unrolled<NRD>([&](auto r) { read1(r, c0, c0); });
+  lds_wait<0>();
+  int kt = 0;
+#pragma unroll 1
+  do {
+    slab(kt);
+  } while (++kt < nk);
+  asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
+  wait_vmcnt<0>();
+  __syncthreads();  // every wave is done reading the stages
+
+  // Epilogue: each wave stages its own tile, 64 rows at a time, through its
+  // own 32 KB (float32 rows of 128, 16-byte chunks XOR-swizzled by row), and
+  // hands 8 consecutive columns at a time to the epilogue: 16 lanes cover a
+  // row's 128 columns.
+  float* cs = reinterpret_cast<float*>(lds) + wave * 8192;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int c8 = lane & 15, n = n0 + wn * 128 + c8 * 8;
+  const bool whole = m0 + 256 <= M && n0 + 256 <= N;
+  unrolled<2>([&](auto hh) {
+    constexpr int h = decltype(hh)::value;
+    unrolled<32>([&](auto ix) {
+      constexpr int i = decltype(ix)::value >> 3, j = decltype(ix)::value & 7;
+      const int r = i * 16 + lr;
+      *reinterpret_cast<f32x4*>(cs + r * 128 + (((j * 4 + lg) ^ (r & 31)) * 4)) = acc[h * 4 + i][j];
+    });
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // Four items at a time: their LDS reads together, and what the epilogue
+    // reads from memory for the next four before these are stored.  Whole
+    // tiles carry no bounds tests.  (One wave per SIMD: an item by itself
+    // costs its LDS latency and tests, 480 cycles against 150 here.)
+    const int mh = m0 + wm * 128 + h * 64 + lg;
+    auto rows = [&](auto full) {
+      constexpr bool FULL = decltype(full)::value;
+      auto inside = [&](int m) { return FULL || (m < M && n < N); };
+      auto group = [&](int g, float(&v)[4][8]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int r = (g * 4 + q) * 4 + lg;
+          const float* row = cs + r * 128;
+          const f32x4 a = *reinterpret_cast<const f32x4*>(row + (((2 * c8) ^ (r & 31)) * 4));
+          const f32x4 b = *reinterpret_cast<const f32x4*>(row + (((2 * c8 + 1) ^ (r & 31)) * 4));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[q][e] = a[e];
+            v[q][4 + e] = b[e];
+          }
+        }
+      };
+      if constexpr (HasPre<Epi>::value) {
+        typename Epi::Pre pre[2][4];
+        auto request = [&](int g, typename Epi::Pre(&to)[4]) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int m = mh + (g * 4 + q) * 4;
+            epi.pre(m, n, inside(m), to[q]);
+          }
+        };
+        request(0, pre[0]);
+#pragma unroll 1
+        for (int gg = 0; gg < 4; gg += 2) {
+          unrolled<2>([&](auto uu) {
+            constexpr int U = decltype(uu)::value;
+            const int g = gg + U;
+            if (g < 3) request(g + 1, pre[U ^ 1]);
+            float v[4][8];
+            group(g, v);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int m = mh + (g * 4 + q) * 4;
+              epi.fin8(m, n, v[q], inside(m), pre[U][q]);
+            }
+          });
+        }
+      } else {
+#pragma unroll 1
+        for (int g = 0; g < 4; ++g) {
+          float v[4][8];
+          group(g, v);
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int m = mh + (g * 4 + q) * 4;
+            epi.apply8(m, n, v[q], inside(m));
+          }
+        }
+      }
+    };
+    if (whole) rows(std::true_type{});
+    else rows(std::false_type{});
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  });
+#endif
+}
+
 // The tied head of the language model, logits z = f E^T, consumed tile by
 // tile and never stored.  EpiHeadStats leaves, for every row of a 128-column
 // tile, (max, sum of exp(z - max)) over the columns below V at
@@ -1073,8 +1451,73 @@ hipError_t launch_pipe_w(const GemmDesc& g, const Epi& epi, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Time model (ns) of a bf16 product with `slabs` 64-deep slabs per
+// workgroup on the two kernels, from 40 measured shapes (M 2048 to 65536,
+// N and K 768 to 3072; within 10 % of them):
+//   128 x 128 tiles, two per CU: 1.17 us per slab and 512 tiles, in
+//     proportion to the tiles (half-filled CUs run faster), 5 us once;
+//   256 x 256 tiles, one per CU: 1.29 us per slab and 8 us of pipeline fill
+//     and epilogue per round of 256 tiles, 4 us once; a partial round costs
+//     about 0.85 of a whole one (the clock rises as CUs idle).
+// An epilogue that also reads memory adds its own time (EpiCost): the large
+// tile has nothing else to run meanwhile.
+struct EpiCost {
+  int64_t pipe;  // per 512 tiles of 128 x 128
+  int64_t wide;  // per 256 tiles of 256 x 256
+};
+template <class Epi>
+constexpr EpiCost epi_cost(const Epi*) { return {0, 0}; }
+template <class T>
+constexpr EpiCost epi_cost(const EpiScore<T>*) { return {1800, 7300}; }
+template <class T>
+constexpr EpiCost epi_cost(const EpiHbar<T>*) { return {2800, 7800}; }
+template <class T>
+constexpr EpiCost epi_cost(const EpiGate<T>*) { return {9900, 22000}; }
+
+int64_t pipe_time(int64_t M, int64_t N, int64_t slabs, int64_t splits, int64_t extra) {
+  const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128) * splits;
+  return 5000 + tiles * (slabs * 1170 + extra) / 512;
+}
+int64_t wide_time(int64_t M, int64_t N, int64_t slabs, int64_t splits, int64_t extra) {
+  const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256) * splits;
+  const int64_t round = slabs * 1290 + 8000 + extra;
+  return 4000 + tiles / 256 * round + (tiles % 256 ? round * 85 / 100 : 0);
+}
+// Whether the 256 x 256 kernel serves a product: B parts that never split a
+// tile, and the smaller modelled time.  Measured, 128 x 128 -> 256 x 256:
+// M = 16384, N = 3072, K = 1024 117 -> 91 us (1.13 PFLOP/s); 1024 x 3072
+// 101 -> 74 us (1.39); M = 65536, N = K = 768 89 -> 76 us; but M = 8192,
+// N = 2304, K = 768 (1.1 rounds) 38.7 -> 44.8 us: it stays on 128 x 128.
+bool wide_ok(const GemmDesc& g, int64_t kchunk, int64_t splits, EpiCost c) {
+  if (g.seg == kSegN && g.seg_len % 256 != 0) return false;
+  return wide_time(g.M, g.N, kchunk / 64, splits, c.wide) <
+         pipe_time(g.M, g.N, kchunk / 64, splits, c.pipe);
+}
+
+template <bool AMC, bool BNC, int SEG, class Epi>
+hipError_t launch_wide(const GemmDesc& g, const Epi& epi, hipStream_t s) {
+  Operand<bf16, AMC, kSegNone> A{{(const bf16*)g.A, nullptr, nullptr}, g.lda, 0};
+  Operand<bf16, BNC, SEG> B{{(const bf16*)g.B[0], (const bf16*)g.B[1], (const bf16*)g.B[2]}, g.ldb,
+                            g.seg_len};
+  int splits = g.splits < 1 ? 1 : g.splits;
+  int kchunk = (g.K + splits - 1) / splits;
+  kchunk = (kchunk + 63) / 64 * 64;
+  if (g.kchunk > 0) kchunk = g.kchunk;
+  splits = (g.K + kchunk - 1) / kchunk;
+  dim3 grid((g.N + 255) / 256, (g.M + 255) / 256, splits);
+  const int group = xcd_group_rows((int)grid.x, (int)grid.y, (int)grid.z);
+  hipLaunchKernelGGL((gemm_wide_kernel<AMC, BNC, SEG, Epi>), grid, dim3(256), 0, s, g.M, g.N, g.K,
+                     A, B, kchunk, group, epi);
+  return hipGetLastError();
+}
+
 template <bool AMC, bool BNC, int SEG, class Epi>
 hipError_t launch_pipe(const GemmDesc& g, const Epi& epi, hipStream_t s) {
+  {
+    const int sp = g.splits < 1 ? 1 : g.splits;
+    const int kc = g.kchunk > 0 ? g.kchunk : ((g.K + sp - 1) / sp + 63) / 64 * 64;
+    if (wide_ok(g, kc, (g.K + kc - 1) / kc, epi_cost((const Epi*)nullptr))) return launch_wide<AMC, BNC, SEG>(g, epi, s);
+  }
   if constexpr (AMC) {
     int splits = g.splits < 1 ? 1 : g.splits;
     if (g.kchunk > 0) splits = (g.K + g.kchunk - 1) / g.kchunk;
@@ -1125,7 +1568,11 @@ namespace {
 // LDS at once), so that the whole grid is resident in one round; every split
 // at least min_k deep in K (rounded to a multiple of 64).  Returns the number
 // of splits; *kchunk is the K range of each.
-static int splitk_plan(int M, int N, int K, int min_k, int* kchunk) {
+// Deep bf16 products (the weight gradients, K = B T >= 16384) are planned
+// for 256 x 256 tiles instead, one workgroup per CU, where the modelled
+// product is faster; wide_ok then takes them there.
+constexpr int kWideSplitK = 16384;
+static int splitk_plan(bool bf, int M, int N, int K, int min_k, int* kchunk) {
   const int tiles = ((M + 127) / 128) * ((N + 127) / 128);
   int sp = 512 / tiles;
   const int kmax = K / min_k;
@@ -1133,6 +1580,17 @@ static int splitk_plan(int M, int N, int K, int min_k, int* kchunk) {
   if (sp < 1) sp = 1;
   int kc = (K + sp - 1) / sp;
   kc = (kc + 63) / 64 * 64;
+  if (bf && K >= kWideSplitK && K % 64 == 0) {
+    const int t256 = ((M + 255) / 256) * ((N + 255) / 256);
+    int sw = 256 / t256;
+    if (sw < 1) sw = 1;
+    const int kw = ((K + sw - 1) / sw + 63) / 64 * 64;
+    sw = (K + kw - 1) / kw;
+    // plus the partial tiles, written and read back at about 4 TB/s
+    const int64_t sn = (K + kc - 1) / kc, part = (int64_t)M * N * 8 / 4000;
+    if (wide_time(M, N, kw / 64, sw, 0) + part * sw < pipe_time(M, N, kc / 64, sn, 0) + part * sn)
+      kc = kw;
+  }
   *kchunk = kc;
   return (K + kc - 1) / kc;
 }
@@ -1188,14 +1646,14 @@ hipError_t dispatch_any(const GemmDesc& g, const Epi& epi, hipStream_t s) {
 
 }  // namespace
 
+// (Both types' plans fit what these two return.)
 int gemm_splitk_splits(int M, int N, int K, int min_k) {
   int kc;
-  return splitk_plan(M, N, K, min_k, &kc);
+  return std::max(splitk_plan(true, M, N, K, min_k, &kc), splitk_plan(false, M, N, K, min_k, &kc));
 }
 
 size_t gemm_splitk_partial_bytes(int M, int N, int K, int min_k) {
-  int kc;
-  const int sp = splitk_plan(M, N, K, min_k, &kc);
+  const int sp = gemm_splitk_splits(M, N, K, min_k);
   return sp > 1 ? (size_t)sp * M * N * sizeof(float) : 0;
 }
 
@@ -1213,7 +1671,7 @@ hipError_t gemm_splitk_product(DType dt, const GemmDesc& g0, float* partial, flo
     return hipErrorInvalidValue;
   GemmDesc g = g0;
   int kc;
-  g.splits = splitk_plan(g.M, g.N, g.K, min_k, &kc);
+  g.splits = splitk_plan(dt == DType::BF16, g.M, g.N, g.K, min_k, &kc);
   g.kchunk = kc;  // exactly g.splits slices of `partial` get written
   *splits = g.splits;
   if (g.splits == 1) {

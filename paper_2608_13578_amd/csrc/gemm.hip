@@ -1267,6 +1267,191 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(int M, int N, int K,
 #endif
 }
 
+// ------------------------------------------------------------------ float32 kernel
+// Four waves (2 x 2) on a BM x BN tile, K in 32-deep slabs through a ring of
+// ST LDS stages filled by direct global->LDS loads, one barrier per slab.
+// float32 matrix instructions are 16 times slower than bf16 ones, so the LDS
+// port is idle most of the time (64 x 64: 256 of 1024 cycles per slab) and
+// small tiles cost nothing there; what bounds the layer's float32 products
+// is the number of workgroups (a 128 x 128 tile gave B T = 4096, D = 512 only
+// 128 of them, a small layer two) and the latency of each slab.  The K order
+// of every sum is that of the 32-deep step of mma16, whatever the tile.
+// Against 128 x 128 tiles staged through registers, B T = 4096, D = 512: Q, K,
+// V 91 -> 64 us (100 TFLOP/s of the 141 a library product of 4096^3
+// reaches), its input gradient 216 -> 60 us; B T = 256, D = 128: products of
+// 13 to 40 us became 4 to 9 us.
+//
+// LDS keeps the global orientation:
+//   K-contiguous operand: [rows][32], 16-byte chunk c of row r at
+//     c ^ ((r / 2) % 8); a lane's eight k values are two 16-byte reads;
+//   M/N-contiguous operand: [32][rows], chunk c of k-row kr at
+//     c ^ 4 ((kr / 8) % 4) (the four lane groups, eight k-rows apart, then
+//     read disjoint banks); a lane's eight k values are eight 4-byte reads.
+template <int R, bool RC>
+struct F32Operand {
+  static constexpr int CPR = RC ? R / 4 : 8;      // 16-byte chunks per LDS row
+  static constexpr int PER = R * 32 / 256 / 4;    // loads per wave per slab
+  static_assert(PER >= 1, "at least one load per wave");
+  __device__ __forceinline__ static int swz(int row) {
+    return RC ? (((row >> 3) & 3) << 2) & (CPR - 1) : (row >> 1) & 7;
+  }
+  uint32_t voff[PER];
+  int r0, rows;  // first row of the tile and rows inside the operand
+
+  __device__ __forceinline__ void setup(int row0, int rmax, int64_t ld, int wave, int lane) {
+    r0 = row0;
+    rows = min(R, rmax - row0);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const int pos = (wave * PER + i) * 64 + lane;
+      const int row = pos / CPR, c = (pos % CPR) ^ swz(row);
+      if constexpr (RC) voff[i] = (uint32_t)(((int64_t)row * ld + min(c * 4, rows - 4)) * 4);
+      else voff[i] = (uint32_t)(((int64_t)min(row, rows - 1) * ld + c * 4) * 4);
+    }
+  }
+  // This wave's loads of the slab at k, kv <= 32 deep, from the operand at P.
+  // The descriptor's extent ends with the slab: k-rows past it read zero.
+  __device__ __forceinline__ void issue(const float* P, int64_t ld, int k, int kv, float* dst,
+                                        int wave) const {
+#if defined(__HIP_DEVICE_COMPILE__)
+    const float* base = RC ? P + (int64_t)k * ld + r0 : P + (int64_t)r0 * ld + k;
+    const int64_t ext = RC ? ((int64_t)(kv - 1) * ld + rows) * 4 : ((int64_t)(rows - 1) * ld + kv) * 4;
+    const __amdgpu_buffer_rsrc_t rs =
+        __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)ext, 0x00020000);
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + (wave * PER + i) * 256), 16,
+                                               voff[i], 0, 0, 0);
+#endif
+  }
+  // A fragment's eight k values of one lane, as the LDS reads leave them.
+  struct Frag8 {
+    f32x4 v[RC ? 1 : 2];
+    float w[RC ? 8 : 1];
+    __device__ __forceinline__ float at(int e) const {
+      if constexpr (RC) return w[e];
+      else return v[e >> 2][e & 3];
+    }
+    // after the wait for the reads
+    __device__ __forceinline__ void bind() {
+      if constexpr (RC) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) lds_tr_bind(w[e]);
+      } else {
+        lds_tr_bind(v[0]);
+        lds_tr_bind(v[1]);
+      }
+    }
+  };
+  // Requests the fragment of rows base .. base + 15.
+  __device__ __forceinline__ static void read(const float* s, int base, int lane, Frag8& f) {
+    const int lr = lane & 15, lg = lane >> 4;
+    if constexpr (!RC) {
+      const int r = base + lr;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        f.v[h] = lds_read_f32x4(s + r * 32 + (((lg * 2 + h) ^ swz(r)) * 4));
+    } else {
+      const int col = base + lr;
+      const float* q = s + lg * 8 * R + (((col >> 2) ^ swz(lg * 8)) * 4) + (col & 3);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) f.w[j] = lds_read_f32(q + j * R);
+    }
+  }
+};
+
+template <int BM, int BN, int ST, bool A_MC, bool B_NC, int BSEG, class Epi>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(int M, int N, int K,
+                                                       Operand<float, A_MC, kSegNone> A,
+                                                       Operand<float, B_NC, BSEG> B, int kchunk,
+                                                       int group, Epi epi0) {
+  typedef F32Operand<BM, A_MC> OA;
+  typedef F32Operand<BN, B_NC> OB;
+  constexpr int BK = 32;
+  constexpr int STAGE = (BM + BN) * BK;  // floats
+  constexpr int WTM = BM / 2, WTN = BN / 2, FM = WTM / 16, FN = WTN / 16;
+  constexpr int NI = OA::PER + OB::PER;
+  static_assert(ST * STAGE >= BM * BN, "the epilogue's tile fits the ring");
+  __shared__ __attribute__((aligned(1024))) float lds[ST * STAGE];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  int tm, tn, z;
+  xcd_tile_order(group, tm, tn, z);
+  const int m0 = tm * BM, n0 = tn * BN;
+  const int kbeg = z * kchunk, kend = min(K, kbeg + kchunk);
+  Epi epi = epi0;
+  bind_split(epi, z);
+  const int nk = (kend - kbeg + BK - 1) / BK;
+
+  const float* bptr = B.p[0];
+  int bn0 = n0, bnmax = N;
+  if constexpr (BSEG == kSegN) {
+    const int sg = n0 / B.seg_len;
+    bptr = sg == 0 ? B.p[0] : sg == 1 ? B.p[1] : B.p[2];
+    bn0 = n0 - sg * B.seg_len;
+    bnmax = B.seg_len;
+  }
+  OA oa;
+  OB ob;
+  oa.setup(m0, M, A.ld, wave, lane);
+  ob.setup(bn0, bnmax, B.ld, wave, lane);
+  auto issue = [&](int kt) {
+    const int k = kbeg + kt * BK, kv = min(BK, kend - k);
+    float* s = lds + (kt % ST) * STAGE;
+    oa.issue(A.p[0], A.ld, k, kv, s, wave);
+    if constexpr (BSEG == kSegK) {
+      const int sl = B.seg_len;
+      const float* p = k < sl ? B.p[0] : k < 2 * sl ? B.p[1] : B.p[2];
+      ob.issue(p, B.ld, k < sl ? k : k < 2 * sl ? k - sl : k - 2 * sl, kv, s + BM * BK, wave);
+    } else {
+      ob.issue(bptr, B.ld, k, kv, s + BM * BK, wave);
+    }
+  };
+
+  f32x4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  const int first = min(ST - 1, nk);
+  for (int kt = 0; kt < first; ++kt) issue(kt);
+  for (int kt = 0; kt < nk; ++kt) {
+    // Slabs up to min(nk, kt + ST - 1) - 1 are requested: slab kt has landed
+    // when at most ST - 2 later ones are outstanding.
+    const int after = min(nk, kt + ST - 1) - 1 - kt;
+    if (ST >= 4 && after >= 2) wait_vmcnt<2 * NI>();
+    else if (ST >= 3 && after >= 1) wait_vmcnt<NI>();
+    else wait_vmcnt<0>();
+    // ... for every wave; and every wave is done reading slab kt - 1
+    __builtin_amdgcn_s_barrier();
+    if (kt + ST - 1 < nk) issue(kt + ST - 1);
+    const float* s = lds + (kt % ST) * STAGE;
+    typename OA::Frag8 fa[FM];
+    typename OB::Frag8 fb[FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i) OA::read(s, wm * WTM + i * 16, lane, fa[i]);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) OB::read(s + BM * BK, wn * WTN + j * 16, lane, fb[j]);
+    lds_tr_wait();
+#pragma unroll
+    for (int i = 0; i < FM; ++i) fa[i].bind();
+#pragma unroll
+    for (int j = 0; j < FN; ++j) fb[j].bind();
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[j].at(e), fa[i].at(e), acc[i][j], 0,
+                                                           0, 0);
+  }
+  staged_epilogue<BM, BN, FM, FN, WTM, WTN, 256>(epi, acc, lds, m0, n0, wm, wn, M, N, tid);
+}
+
 // The tied head of the language model, logits z = f E^T, consumed tile by
 // tile and never stored.  EpiHeadStats leaves, for every row of a 128-column
 // tile, (max, sum of exp(z - max)) over the columns below V at
@@ -1423,6 +1608,37 @@ hipError_t launch(const GemmDesc& g, const Epi& epi, hipStream_t s) {
   return hipGetLastError();
 }
 
+// float32 launch: 64 x 64 tiles, or 32 x 64 where those would not give every
+// CU a workgroup (a small layer's B T = 256, D = 128 then has 16 to 48
+// workgroups instead of 2 to 6).  A product whose K may end inside a slab has
+// both operands M/N-contiguous.
+template <int BM, int ST, bool AMC, bool BNC, int SEG, class Epi>
+hipError_t launch_f32_tile(const GemmDesc& g, const Epi& epi, int kchunk, int splits,
+                           hipStream_t s) {
+  Operand<float, AMC, kSegNone> A{{(const float*)g.A, nullptr, nullptr}, g.lda, 0};
+  Operand<float, BNC, SEG> B{{(const float*)g.B[0], (const float*)g.B[1], (const float*)g.B[2]},
+                             g.ldb, g.seg_len};
+  const dim3 grid((g.N + 63) / 64, (g.M + BM - 1) / BM, splits);
+  const int group = xcd_group_rows((int)grid.x, (int)grid.y, (int)grid.z);
+  hipLaunchKernelGGL((gemm_f32_kernel<BM, 64, ST, AMC, BNC, SEG, Epi>), grid, dim3(256), 0, s, g.M,
+                     g.N, g.K, A, B, kchunk, group, epi);
+  return hipGetLastError();
+}
+
+template <bool AMC, bool BNC, int SEG, class Epi>
+hipError_t launch_f32(const GemmDesc& g, const Epi& epi, hipStream_t s) {
+  if (!(AMC && BNC) && g.K % 32 != 0) return hipErrorInvalidValue;
+  if ((AMC && g.M < 4) || g.N < 4) return hipErrorInvalidValue;
+  if (SEG != kSegNone && g.seg_len % 64 != 0) return hipErrorInvalidValue;
+  int splits = g.splits < 1 ? 1 : g.splits;
+  int kchunk = ((g.K + splits - 1) / splits + 31) / 32 * 32;
+  if (g.kchunk > 0) kchunk = g.kchunk;
+  splits = (g.K + kchunk - 1) / kchunk;
+  const int64_t tiles = (int64_t)((g.N + 63) / 64) * ((g.M + 63) / 64) * splits;
+  if (tiles < 256) return launch_f32_tile<32, 4, AMC, BNC, SEG>(g, epi, kchunk, splits, s);
+  return launch_f32_tile<64, 3, AMC, BNC, SEG>(g, epi, kchunk, splits, s);
+}
+
 // Pipelined bf16 launch: 128 x 128 tiles, two 32 KB slabs in flight, so
 // that two workgroups share a CU (measured faster on these shapes than a
 // deeper ring with one workgroup per CU).  Eight waves of 64 x 32 by
@@ -1530,6 +1746,7 @@ hipError_t launch_pipe(const GemmDesc& g, const Epi& epi, hipStream_t s) {
 
 template <typename T, bool AMC, bool BNC, int SEG, class Epi>
 hipError_t launch_any(const GemmDesc& g, const Epi& epi, hipStream_t s) {
+  if constexpr (sizeof(T) == 4) return launch_f32<AMC, BNC, SEG>(g, epi, s);
   if constexpr (sizeof(T) == 2) {
     // The pipelined kernel needs whole 64-deep slabs, operands of at least
     // 8 rows, and B parts that never split a tile (N) or a slab (K).
@@ -1537,8 +1754,8 @@ hipError_t launch_any(const GemmDesc& g, const Epi& epi, hipStream_t s) {
     if (SEG == kSegN) ok = ok && g.seg_len % 128 == 0;
     if (SEG == kSegK) ok = ok && g.seg_len % 64 == 0;
     if (ok) return launch_pipe<AMC, BNC, SEG>(g, epi, s);
+    return launch<T, AMC, BNC, SEG>(g, epi, s);
   }
-  return launch<T, AMC, BNC, SEG>(g, epi, s);
 }
 
 template <typename T, class Epi>
@@ -1717,7 +1934,7 @@ hipError_t gemm_score(DType dt, const GemmDesc& g, void* C, const void* wp, floa
   if (dt == DType::BF16)
     return launch_any<bf16, false, true, kSegNone>(
         g, EpiScore<bf16>{(bf16*)C, g.N, (const bf16*)wp, sp, g.N / 64}, s);
-  return launch<float, false, true, kSegNone>(
+  return launch_f32<false, true, kSegNone>(
       g, EpiScore<float>{(float*)C, g.N, (const float*)wp, sp, g.N / 64}, s);
 }
 
@@ -1725,7 +1942,7 @@ hipError_t gemm_gate(DType dt, const GemmDesc& g, const GateEpi& e, hipStream_t 
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (!(!g.a_mcontig && g.b_ncontig && g.seg == kSegNone)) return hipErrorInvalidValue;
   if (dt == DType::BF16) return launch_any<bf16, false, true, kSegNone>(g, EpiGate<bf16>{e}, s);
-  return launch<float, false, true, kSegNone>(g, EpiGate<float>{e}, s);
+  return launch_f32<false, true, kSegNone>(g, EpiGate<float>{e}, s);
 }
 
 hipError_t gemm_gelu(DType dt, const GemmDesc& g, void* U, void* A, int64_t ld, hipStream_t s) {
@@ -1769,7 +1986,7 @@ hipError_t gemm_hbar(DType dt, const GemmDesc& g, const HbarEpi& e, hipStream_t 
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (!(!g.a_mcontig && !g.b_ncontig && g.seg == kSegNone)) return hipErrorInvalidValue;
   if (dt == DType::BF16) return launch_any<bf16, false, false, kSegNone>(g, EpiHbar<bf16>{e}, s);
-  return launch<float, false, false, kSegNone>(g, EpiHbar<float>{e}, s);
+  return launch_f32<false, false, kSegNone>(g, EpiHbar<float>{e}, s);
 }
 
 }  // namespace bcmt

@@ -3,21 +3,21 @@
 // Serves every dense projection of the layer (Sec. 3.3 Q/K/V and W_O,
 // Sec. 3.5 W_m, Sec. 3.8 W_g) and their backward products.
 //
-// Two kernels:
-//  * gemm_pipe_kernel (bf16): 128 x 128 tiles, four waves of 64 x 64, K
-//    streamed in 64-deep slabs through a two-slab LDS ring filled by direct
-//    global->LDS loads; operands stay in their global orientation in LDS and
-//    M/N-major ones are read with the transposing LDS instruction.  Two
-//    workgroups share a CU.  Tiles are ordered per XCD (see xcd_tile_order).
-//  * gemm_kernel (float32, and bf16 shapes whose K is not a multiple of 64):
-//    the same tiling with register staging; M/N-major operands are
-//    transposed in registers on their way into LDS.
+// Kernels (a rule on sizes picks one, see the launchers):
+//  * gemm_pipe_kernel (bf16): 128 x 128 tiles, K streamed in 64-deep slabs
+//    through a two-slab LDS ring filled by direct global->LDS loads; operands
+//    stay in their global orientation in LDS and M/N-major ones are read with
+//    the transposing LDS instruction.  Two workgroups share a CU.  Tiles are
+//    ordered per XCD (see xcd_tile_order).  Small products take 32 x 128
+//    tiles with four slabs in flight.
+//  * gemm_wide_kernel (bf16): 256 x 256 tiles for large products.
+//  * gemm_f32_kernel (float32): 64 x 64 or 32 x 64 tiles.
 // Weight gradients (K = B*T) use split-K partial tiles and a deterministic
 // reduction kernel instead of atomics.
 //
 // The matrix instruction is issued with the B tile as its first operand, so
-// a lane ends up holding four consecutive output columns of one output row:
-// the epilogue stores 8 (bf16) or 16 (f32) contiguous bytes per lane.
+// a lane ends up holding four consecutive output columns of one output row;
+// the epilogue goes through LDS and takes 8 consecutive columns at a time.
 #include <algorithm>
 #include <type_traits>
 #include <utility>
@@ -28,212 +28,16 @@
 namespace bcmt {
 namespace {
 
-constexpr int kThreads = 256;
-constexpr int BM = 128;
-constexpr int BN = 128;
-
-template <typename T> struct KSlab;
-template <> struct KSlab<bf16> { static constexpr int BK = 64; };
-template <> struct KSlab<float> { static constexpr int BK = 32; };
-
 // An operand indexed by (row, k), where row is m for A and n for B.
 template <typename T, bool RCONTIG, int SEG>
 struct Operand {
   const T* p[3];
   int64_t ld;
   int seg_len;
-  __device__ __forceinline__ const T* at(int row, int k) const {
-    int s = 0;
-    if constexpr (SEG == kSegN) {
-      s = row / seg_len;
-      row -= s * seg_len;
-    } else if constexpr (SEG == kSegK) {
-      s = k / seg_len;
-      k -= s * seg_len;
-    }
-    return p[s] + (RCONTIG ? (int64_t)k * ld + row : (int64_t)row * ld + k);
-  }
 };
-
-// Registers holding one operand's share of a K slab between its global load
-// and its LDS store.
-template <typename T, bool RCONTIG, int SEG, int R>
-struct Stage {
-  static constexpr int VE = Vec16<T>::N;
-  static constexpr int BK = KSlab<T>::BK;
-  static constexpr int LDS_ROW = BK + VE;
-  typedef typename Vec16<T>::type vec;
-  // K-contiguous: R rows of BK/VE vectors.  Row-contiguous: (BK/VE) x (R/VE)
-  // sub-blocks of VE x VE elements, at most one per thread.
-  static constexpr int NV = RCONTIG ? VE : (R * (BK / VE)) / kThreads;
-  static constexpr int NSB = (BK / VE) * (R / VE);
-  static_assert(RCONTIG ? NSB <= kThreads : (R * (BK / VE)) % kThreads == 0, "tile");
-  vec r[NV];
-
-  __device__ __forceinline__ void load(const Operand<T, RCONTIG, SEG>& op, int row0, int rmax,
-                                       int k0, int kend, int tid) {
-    if constexpr (!RCONTIG) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const int idx = tid + v * kThreads;
-        const int rr = idx / (BK / VE);
-        const int cc = (idx % (BK / VE)) * VE;
-        const int gr = row0 + rr, gk = k0 + cc;
-        if (gr < rmax && gk < kend) r[v] = load16(op.at(gr, gk));
-        else r[v] = vec{};
-      }
-    } else {
-      if (tid < NSB) {
-        const int kb = tid / (R / VE);
-        const int rb = tid % (R / VE);
-        const int gr = row0 + rb * VE;
-#pragma unroll
-        for (int j = 0; j < VE; ++j) {
-          const int gk = k0 + kb * VE + j;
-          if (gr < rmax && gk < kend) r[j] = load16(op.at(gr, gk));
-          else r[j] = vec{};
-        }
-      }
-    }
-  }
-
-  __device__ __forceinline__ void store(T* lds, int tid) const {
-    if constexpr (!RCONTIG) {
-#pragma unroll
-      for (int v = 0; v < NV; ++v) {
-        const int idx = tid + v * kThreads;
-        const int rr = idx / (BK / VE);
-        const int cc = (idx % (BK / VE)) * VE;
-        store16(lds + rr * LDS_ROW + cc, r[v]);
-      }
-    } else {
-      if (tid < NSB) {
-        const int kb = tid / (R / VE);
-        const int rb = tid % (R / VE);
-#pragma unroll
-        for (int i = 0; i < VE; ++i) {
-          vec t;
-#pragma unroll
-          for (int j = 0; j < VE; ++j) t[j] = r[j][i];
-          store16(lds + (rb * VE + i) * LDS_ROW + kb * VE, t);
-        }
-      }
-    }
-  }
-};
-
-template <typename T, bool A_MC, bool B_NC, int BSEG, class Epi>
-__global__ __launch_bounds__(kThreads) void gemm_kernel(int M, int N, int K,
-                                                        Operand<T, A_MC, kSegNone> A,
-                                                        Operand<T, B_NC, BSEG> B, int kchunk,
-                                                        Epi epi0) {
-  constexpr int BK = KSlab<T>::BK;
-  constexpr int VE = Vec16<T>::N;
-  constexpr int LDS_ROW = BK + VE;
-  __shared__ __attribute__((aligned(16))) T As[2][BM * LDS_ROW];
-  __shared__ __attribute__((aligned(16))) T Bs[2][BN * LDS_ROW];
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int lr = lane & 15, lg = lane >> 4;
-  const int m0 = blockIdx.y * BM, n0 = blockIdx.x * BN;
-  const int kbeg = blockIdx.z * kchunk;
-  Epi epi = epi0;
-  bind_split(epi, blockIdx.z);
-  const int kend = min(K, kbeg + kchunk);
-  const int nk = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
-
-  Stage<T, A_MC, kSegNone, BM> sa;
-  Stage<T, B_NC, BSEG, BN> sb;
-  f32x4 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  if (nk > 0) {
-    sa.load(A, m0, M, kbeg, kend, tid);
-    sb.load(B, n0, N, kbeg, kend, tid);
-    sa.store(As[0], tid);
-    sb.store(Bs[0], tid);
-  }
-  __syncthreads();
-
-  for (int kt = 0; kt < nk; ++kt) {
-    const int cur = kt & 1;
-    const bool more = kt + 1 < nk;
-    if (more) {
-      const int k0 = kbeg + (kt + 1) * BK;
-      sa.load(A, m0, M, k0, kend, tid);
-      sb.load(B, n0, N, k0, kend, tid);
-    }
-    const T* as = As[cur];
-    const T* bs = Bs[cur];
-#pragma unroll
-    for (int ks = 0; ks < BK / 32; ++ks) {
-      typename Frag<T>::type fa[4], fb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        fa[i] = load_frag(as + (wm * 64 + i * 16 + lr) * LDS_ROW + ks * 32 + lg * 8);
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        fb[j] = load_frag(bs + (wn * 64 + j * 16 + lr) * LDS_ROW + ks * 32 + lg * 8);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = mma16(fb[j], fa[i], acc[i][j]);
-    }
-    if (more) {
-      sa.store(As[cur ^ 1], tid);
-      sb.store(Bs[cur ^ 1], tid);
-    }
-    __syncthreads();
-  }
-
-  run_epilogue<4, 4>(epi, acc, m0 + wm * 64, n0 + wn * 64, M, N, lane);
-}
 
 // ------------------------------------------------------------------ epilogue driver
-// Hands every fragment of a wave's tile to the epilogue.  An epilogue with
-// kRowDot also folds each fragment into a per-row value (rowdot) that is
-// summed over the wave's columns and handed to row() once per row, by the
-// lane group holding the row's first four columns.
-template <class Epi, class = void>
-struct HasRowDot {
-  static constexpr bool value = false;
-};
-template <class Epi>
-struct HasRowDot<Epi, decltype((void)Epi::kRowDot)> {
-  static constexpr bool value = Epi::kRowDot;
-};
-
-template <int FM, int FN, class Epi>
-__device__ __forceinline__ void run_epilogue(const Epi& epi, const f32x4 (&acc)[FM][FN], int mb,
-                                             int nb, int M, int N, int lane) {
-  const int lr = lane & 15, lg = lane >> 4;
-#pragma unroll
-  for (int i = 0; i < FM; ++i) {
-    const int m = mb + i * 16 + lr;
-    float rs = 0.f;
-#pragma unroll
-    for (int j = 0; j < FN; ++j) {
-      const int n = nb + j * 16 + lg * 4;
-      if (m < M && n < N) {
-        epi(m, n, acc[i][j]);
-        if constexpr (HasRowDot<Epi>::value) rs += epi.rowdot(n, acc[i][j]);
-      }
-    }
-    if constexpr (HasRowDot<Epi>::value) {
-      rs += __shfl_xor(rs, 16);
-      rs += __shfl_xor(rs, 32);
-      if (lg == 0 && m < M && nb < N) epi.row(m, nb, rs);
-    }
-  }
-}
-
-// 8 consecutive elements to / from float (16 bytes of bf16, 32 of float).
-// Staged epilogue of the pipelined kernel.  The accumulator tile goes to
+// Staged epilogue.  The accumulator tile goes to
 // LDS (float32, rows of BN, 16-byte chunks XOR-swizzled by row so that the
 // 16 rows a fragment spans fall on distinct banks), then every thread hands
 // 8 consecutive columns of a row at a time to the epilogue's apply8: the
@@ -327,10 +131,6 @@ struct EpiStore {
     for (int e = 0; e < 8; ++e) o[e] = v[e] + p.a.at(e);
     st8(c, o);
   }
-  __device__ __forceinline__ void operator()(int m, int n, f32x4 v) const {
-    if (add) v += load4f(add + (int64_t)m * ld_add + n);
-    store4(C + (int64_t)m * ldc + n, v[0], v[1], v[2], v[3]);
-  }
   __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
     Pre p;
     pre(m, n, ok, p);
@@ -356,17 +156,6 @@ struct EpiGelu {
   T* U;
   T* A;
   int64_t ld;
-  __device__ __forceinline__ void operator()(int m, int n, f32x4 v) const {
-    const int64_t off = (int64_t)m * ld + n;
-    f32x4 a;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      v[r] = (float)(T)v[r];
-      a[r] = gelu_f(v[r]);
-    }
-    store4(U + off, v[0], v[1], v[2], v[3]);
-    store4(A + off, a[0], a[1], a[2], a[3]);
-  }
   __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
     if (!ok) return;
     const int64_t off = (int64_t)m * ld + n;
@@ -401,13 +190,6 @@ struct EpiGeluBwd {
     for (int k = 0; k < 8; ++k) d[k] = v[k] * gelu_grad_f(p.u.at(k));
     st8(dU + (int64_t)m * ld + n, d);
   }
-  __device__ __forceinline__ void operator()(int m, int n, f32x4 v) const {
-    const int64_t off = (int64_t)m * ld + n;
-    const f32x4 u = load4f(U + off);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] *= gelu_grad_f(u[r]);
-    store4(dU + off, v[0], v[1], v[2], v[3]);
-  }
   __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
     Pre p;
     pre(m, n, ok, p);
@@ -426,20 +208,6 @@ struct EpiScore {
   const T* wp;
   float* sp;
   int nparts;
-  static constexpr bool kRowDot = true;
-  __device__ __forceinline__ void operator()(int m, int n, f32x4 v) const {
-    store4(C + (int64_t)m * ldc + n, v[0], v[1], v[2], v[3]);
-  }
-  __device__ __forceinline__ float rowdot(int n, f32x4 v) const {
-    const f32x4 w = load4f(wp + n);
-    float d = 0.f;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) d += to_f32(from_f32<T>(v[r])) * w[r];
-    return d;
-  }
-  __device__ __forceinline__ void row(int m, int n0, float v) const {
-    sp[(int64_t)m * nparts + n0 / 64] = v;
-  }
   // The 8 lanes holding one row's 64-column group (n0 a multiple of 64) are
   // consecutive and aligned, so the group's dot is a reduction over them.
   __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
@@ -466,9 +234,6 @@ struct EpiPartial {
   float* P;
   int64_t ld;
   int64_t split_stride;
-  __device__ __forceinline__ void operator()(int m, int n, f32x4 v) const {
-    store4(P + (int64_t)m * ld + n, v[0], v[1], v[2], v[3]);
-  }
   __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
     if (ok) st8(P + (int64_t)m * ld + n, v);
   }
@@ -522,26 +287,6 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
 template <typename T>
 struct EpiGate {
   GateEpi e;
-  __device__ __forceinline__ void operator()(int m, int n, f32x4 u) const {
-    const int b = m / e.T;
-    const int t = m - b * e.T;
-    const int blk = t / e.L;
-    const int64_t off = (int64_t)m * e.D + n;
-    const f32x4 h = load4f(reinterpret_cast<const T*>(e.H) + off);
-    f32x4 c = {0.f, 0.f, 0.f, 0.f};
-    if (blk > 0) c = load4f(e.P + (int64_t)(b * e.nb + blk - 1) * e.D + n);
-    else if (e.Pc) c = load4f(e.Pc + (int64_t)b * e.D + n);
-    f32x4 x = {0.f, 0.f, 0.f, 0.f};
-    if (e.X) x = load4f(reinterpret_cast<const T*>(e.X) + off);
-    f32x4 g, y;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      g[r] = sigmoidf_(u[r]);
-      y[r] = h[r] + g[r] * c[r] + x[r];
-    }
-    store4(reinterpret_cast<T*>(e.Y) + off, y[0], y[1], y[2], y[3]);
-    store4(reinterpret_cast<typename GateT<T>::type*>(e.G) + off, g[0], g[1], g[2], g[3]);
-  }
   struct Pre {
     Raw8<T> h, x;
     Raw8<float> c;
@@ -585,20 +330,6 @@ struct EpiGate {
 template <typename T>
 struct EpiHbar {
   HbarEpi e;
-  __device__ __forceinline__ void operator()(int m, int n, f32x4 v) const {
-    const int b = m / e.T;
-    const int t = m - b * e.T;
-    const int blk = t / e.L;
-    const int64_t off = (int64_t)m * e.D + n;
-    const f32x4 dy = load4f(reinterpret_cast<const T*>(e.dY) + off);
-    const f32x4 dS = load4f(e.dS + (int64_t)(b * e.nb + blk) * e.D + n);
-    const f32x4 w = load4f(reinterpret_cast<const T*>(e.wp) + n);
-    const float a = e.a[m], ds = e.ds[m];
-    f32x4 o;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) o[r] = v[r] + dy[r] + a * dS[r] + ds * w[r];
-    store4(reinterpret_cast<T*>(e.dH) + off, o[0], o[1], o[2], o[3]);
-  }
   struct Pre {
     Raw8<T> dy, w;
     Raw8<float> dS;
@@ -696,7 +427,8 @@ struct PipeLoad {
   static constexpr int PER = Op::INSTR / NW;  // loads per wave per slab
   static_assert(Op::INSTR % NW == 0, "loads per wave");
   uint32_t voff[PER];
-  uint32_t extent;  // bytes a slab may touch from its base
+  uint32_t extent;  // bytes a whole slab may touch from its base
+  uint32_t pitch;   // bytes from one k-row to the next (row-contiguous)
   int r0, c0;
 
   __device__ __forceinline__ void setup(int row0, int rmax, int64_t ld, int wave, int lane) {
@@ -712,6 +444,7 @@ struct PipeLoad {
         voff[i] = (uint32_t)(((int64_t)rr * ld + cg * 8) * 2);
       }
       extent = (uint32_t)(((int64_t)(nrows - 1) * ld + BK) * 2);
+      pitch = 0;
     } else {
       constexpr int CPR = R / 8;     // 16-byte chunks per k-row
       constexpr int RPI = 64 / CPR;  // k-rows per load instruction
@@ -726,7 +459,14 @@ struct PipeLoad {
         voff[i] = (uint32_t)(((int64_t)kr * ld + (gc - c0)) * 2);
       }
       extent = (uint32_t)(((int64_t)(BK - 1) * ld + (cend - c0)) * 2);
+      pitch = (uint32_t)(ld * 2);
     }
+  }
+  // Bytes the slab at k may touch: of a last, partial slab only the k-rows
+  // below kend (row-contiguous; the others then read as zero).
+  __device__ __forceinline__ uint32_t extent_at(int k, int kend) const {
+    if constexpr (!RCONTIG) return extent;
+    else return extent - (uint32_t)max(0, k + BK - kend) * pitch;
   }
 
   // Base of the slab starting at k (relative to pointer P).
@@ -737,10 +477,11 @@ struct PipeLoad {
 
   // This wave's loads of one slab into dst (the operand's LDS region).
   // (The buffer-descriptor type exists only in the device compilation pass.)
-  __device__ __forceinline__ void issue(const bf16* base, bf16* dst, int wave) const {
+  __device__ __forceinline__ void issue(const bf16* base, uint32_t ext, bf16* dst,
+                                        int wave) const {
 #if defined(__HIP_DEVICE_COMPILE__)
     const __amdgpu_buffer_rsrc_t rs =
-        __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)extent, 0x00020000);
+        __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)ext, 0x00020000);
 #pragma unroll
     for (int i = 0; i < PER; ++i)
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_void_t*)(dst + (wave * PER + i) * 512), 16,
@@ -749,9 +490,8 @@ struct PipeLoad {
   }
 
 #if defined(__HIP_DEVICE_COMPILE__)
-  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const bf16* base, bool on) const {
-    return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, on ? (int)extent : 0,
-                                             0x00020000);
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc(const bf16* base, uint32_t ext) const {
+    return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)ext, 0x00020000);
   }
   // The i-th of this wave's loads of one slab.
   template <int I>
@@ -836,22 +576,24 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
   const int wm = wave / WGN, wn = wave % WGN;
   int tm, tn, z;
   xcd_tile_order(group, tm, tn, z);
-  const int m0 = tm * BM, n0 = tn * BN;
+  const int m0 = tm * BM;
   const int kbeg = z * kchunk;
   Epi epi = epi0;
   bind_split(epi, z);
   const int kend = min(K, kbeg + kchunk);
-  const int nk = kend > kbeg ? (kend - kbeg) / BK : 0;
+  const int nk = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
 
-  // B split along N: the tile lies inside one part (the launcher checks that
-  // the part width is a multiple of BN).
+  // B split along N: every part has column tiles of its own (the last one
+  // partial where the part width is no multiple of BN).
   const bf16* bptr = B.p[0];
-  int bn0 = n0, bnmax = N;
+  int n0 = tn * BN, bn0 = n0, bnmax = N, nend = N;
   if constexpr (BSEG == kSegN) {
-    const int sg = n0 / B.seg_len;
-    bptr = B.p[sg];
-    bn0 = n0 - sg * B.seg_len;
+    const int per = (B.seg_len + BN - 1) / BN, sg = tn / per;
+    bptr = sg == 0 ? B.p[0] : sg == 1 ? B.p[1] : B.p[2];
+    bn0 = (tn - sg * per) * BN;
+    n0 = sg * B.seg_len + bn0;
     bnmax = B.seg_len;
+    nend = (sg + 1) * B.seg_len;
   }
   LA la;
   LB lb;
@@ -925,8 +667,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
     if (st < nk) {
       bf16* sa = lds + st * STAGE;
       const int k = kbeg + st * BK;
-      la.issue(la.slab(A.p[0], A.ld, k), sa, wave);
-      lb.issue(bslab(k), sa + AEL, wave);
+      la.issue(la.slab(A.p[0], A.ld, k), la.extent_at(k, kend), sa, wave);
+      lb.issue(bslab(k), lb.extent_at(k, kend), sa + AEL, wave);
     }
   }
   if (nk > 0) {
@@ -957,8 +699,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
             if (nxt < nk) {
               bf16* sn = buf(kt);
               const int k = kbeg + nxt * BK;
-              la.issue(la.slab(A.p[0], A.ld, k), sn, wave);
-              lb.issue(bslab(k), sn + AEL, wave);
+              la.issue(la.slab(A.p[0], A.ld, k), la.extent_at(k, kend), sn, wave);
+              lb.issue(bslab(k), lb.extent_at(k, kend), sn + AEL, wave);
             }
             read_step(buf(kt + 1), 0, fa[c ^ 1], fb[c ^ 1]);
           }
@@ -971,7 +713,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
 
   static_assert(STAGES * STAGE * 2 >= BM * BN * 4, "staging tile fits the LDS ring");
   staged_epilogue<BM, BN, FM, FN, WTM, WTN, NW * 64>(epi, acc, reinterpret_cast<float*>(lds), m0,
-                                                      n0, wm, wn, M, N, tid);
+                                                      n0, wm, wn, M, nend, tid);
 }
 
 // ------------------------------------------------------------------ wide kernel
@@ -1057,20 +799,22 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(int M, int N, int K,
   const int wm = wave >> 1, wn = wave & 1;
   int tm, tn, z;
   xcd_tile_order(group, tm, tn, z);
-  const int m0 = tm * 256, n0 = tn * 256;
+  const int m0 = tm * 256;
   const int kbeg = z * kchunk;
   Epi epi = epi0;
   bind_split(epi, z);
   const int kend = min(K, kbeg + kchunk);
-  const int nk = kend > kbeg ? (kend - kbeg) / BK : 0;
+  const int nk = (kend - kbeg + BK - 1) / BK;  // at least 1
 
   const bf16* bptr = B.p[0];
-  int bn0 = n0, bnmax = N;
+  int n0 = tn * 256, bn0 = n0, bnmax = N, nend = N;
   if constexpr (BSEG == kSegN) {
-    const int sg = n0 / B.seg_len;
-    bptr = B.p[sg];
-    bn0 = n0 - sg * B.seg_len;
+    const int per = (B.seg_len + 255) / 256, sg = tn / per;
+    bptr = sg == 0 ? B.p[0] : sg == 1 ? B.p[1] : B.p[2];
+    bn0 = (tn - sg * per) * 256;
+    n0 = sg * B.seg_len + bn0;
     bnmax = B.seg_len;
+    nend = (sg + 1) * B.seg_len;
   }
   LA la;
   LB lb;
@@ -1126,8 +870,9 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(int M, int N, int K,
   auto slab = [&](int kt) {
     const bool load = kt + 2 < nk;
     const int k = kbeg + (load ? kt + 2 : kt) * BK;
-    const __amdgpu_buffer_rsrc_t rsa = la.rsrc(la.slab(A.p[0], A.ld, k), load);
-    const __amdgpu_buffer_rsrc_t rsb = lb.rsrc(bslab(k), load);
+    const __amdgpu_buffer_rsrc_t rsa =
+        la.rsrc(la.slab(A.p[0], A.ld, k), load ? la.extent_at(k, kend) : 0);
+    const __amdgpu_buffer_rsrc_t rsb = lb.rsrc(bslab(k), load ? lb.extent_at(k, kend) : 0);
     bf16* sa = lds + (kt & 1) * kStage;
     asm volatile("s_nop 2");
     unrolled<64>([&](auto ix) {
@@ -1168,8 +913,8 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(int M, int N, int K,
 #pragma unroll
   for (int st = 0; st < 2; ++st) {
     const int k = kbeg + min(st, nk - 1) * BK;
-    la.issue(la.slab(A.p[0], A.ld, k), lds + st * kStage, wave);
-    lb.issue(bslab(k), lds + (2 + st) * kStage, wave);
+    la.issue(la.slab(A.p[0], A.ld, k), la.extent_at(k, kend), lds + st * kStage, wave);
+    lb.issue(bslab(k), lb.extent_at(k, kend), lds + (2 + st) * kStage, wave);
   }
   wait_vmcnt<NLD>();
   __builtin_amdgcn_s_barrier();
@@ -1191,7 +936,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(int M, int N, int K,
   float* cs = reinterpret_cast<float*>(lds) + wave * 8192;
   const int lr = lane & 15, lg = lane >> 4;
   const int c8 = lane & 15, n = n0 + wn * 128 + c8 * 8;
-  const bool whole = m0 + 256 <= M && n0 + 256 <= N;
+  const bool whole = m0 + 256 <= M && n0 + 256 <= nend;
   unrolled<2>([&](auto hh) {
     constexpr int h = decltype(hh)::value;
     unrolled<32>([&](auto ix) {
@@ -1207,7 +952,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(int M, int N, int K,
     const int mh = m0 + wm * 128 + h * 64 + lg;
     auto rows = [&](auto full) {
       constexpr bool FULL = decltype(full)::value;
-      auto inside = [&](int m) { return FULL || (m < M && n < N); };
+      auto inside = [&](int m) { return FULL || (m < M && n < nend); };
       auto group = [&](int g, float(&v)[4][8]) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -1589,23 +1334,10 @@ int xcd_group_rows(int nx, int ny, int nz) {
   return g;
 }
 
-template <typename T, bool AMC, bool BNC, int SEG, class Epi>
-hipError_t launch(const GemmDesc& g, const Epi& epi, hipStream_t s) {
-  constexpr int BK = KSlab<T>::BK;
-  Operand<T, AMC, kSegNone> A{{(const T*)g.A, nullptr, nullptr}, g.lda, 0};
-  Operand<T, BNC, SEG> B{{(const T*)g.B[0], (const T*)g.B[1], (const T*)g.B[2]}, g.ldb,
-                         g.seg_len};
-  int splits = g.splits < 1 ? 1 : g.splits;
-  int kchunk = (g.K + splits - 1) / splits;
-  kchunk = (kchunk + BK - 1) / BK * BK;
-  if (kchunk < BK) kchunk = BK;
-  if (g.kchunk > 0) kchunk = g.kchunk;
-  splits = (g.K + kchunk - 1) / kchunk;
-  if (splits < 1) splits = 1;
-  dim3 grid((g.N + BN - 1) / BN, (g.M + BM - 1) / BM, splits);
-  hipLaunchKernelGGL((gemm_kernel<T, AMC, BNC, SEG, Epi>), grid, dim3(kThreads), 0, s, g.M, g.N,
-                     g.K, A, B, kchunk, epi);
-  return hipGetLastError();
+// Column tiles of width bn: those of every part where B is split along N.
+int64_t col_tiles(const GemmDesc& g, int bn) {
+  if (g.seg == kSegN) return (int64_t)(g.N / g.seg_len) * ((g.seg_len + bn - 1) / bn);
+  return (g.N + bn - 1) / bn;
 }
 
 // float32 launch: 64 x 64 tiles, or 32 x 64 where those would not give every
@@ -1649,9 +1381,9 @@ hipError_t launch_f32(const GemmDesc& g, const Epi& epi, hipStream_t s) {
 // input gradient of Q, K, V): there eight waves measured slower.  The
 // layer's forward + backward step took 308 instead of 316 us.  Needs the K
 // range of every split to be a whole number of 64-wide slabs.
-template <int WGM, int WGN, bool AMC, bool BNC, int SEG, class Epi>
+template <int PBM, int ST, int WGM, int WGN, bool AMC, bool BNC, int SEG, class Epi>
 hipError_t launch_pipe_w(const GemmDesc& g, const Epi& epi, hipStream_t s) {
-  constexpr int PBM = 128, PBN = 128, PBK = 64, ST = 2;
+  constexpr int PBN = 128, PBK = 64;
   Operand<bf16, AMC, kSegNone> A{{(const bf16*)g.A, nullptr, nullptr}, g.lda, 0};
   Operand<bf16, BNC, SEG> B{{(const bf16*)g.B[0], (const bf16*)g.B[1], (const bf16*)g.B[2]}, g.ldb,
                             g.seg_len};
@@ -1660,7 +1392,7 @@ hipError_t launch_pipe_w(const GemmDesc& g, const Epi& epi, hipStream_t s) {
   kchunk = (kchunk + 63) / 64 * 64;
   if (g.kchunk > 0) kchunk = g.kchunk;
   splits = (g.K + kchunk - 1) / kchunk;
-  dim3 grid((g.N + PBN - 1) / PBN, (g.M + PBM - 1) / PBM, splits);
+  dim3 grid((unsigned)col_tiles(g, PBN), (g.M + PBM - 1) / PBM, splits);
   const int group = xcd_group_rows((int)grid.x, (int)grid.y, (int)grid.z);
   hipLaunchKernelGGL((gemm_pipe_kernel<PBM, PBN, PBK, ST, WGM, WGN, AMC, BNC, SEG, Epi>), grid,
                      dim3(WGM * WGN * 64), 0, s, g.M, g.N, g.K, A, B, kchunk, group, epi);
@@ -1690,24 +1422,22 @@ constexpr EpiCost epi_cost(const EpiHbar<T>*) { return {2800, 7800}; }
 template <class T>
 constexpr EpiCost epi_cost(const EpiGate<T>*) { return {9900, 22000}; }
 
-int64_t pipe_time(int64_t M, int64_t N, int64_t slabs, int64_t splits, int64_t extra) {
-  const int64_t tiles = ((M + 127) / 128) * ((N + 127) / 128) * splits;
+int64_t pipe_time(int64_t M, int64_t cols, int64_t slabs, int64_t splits, int64_t extra) {
+  const int64_t tiles = ((M + 127) / 128) * cols * splits;
   return 5000 + tiles * (slabs * 1170 + extra) / 512;
 }
-int64_t wide_time(int64_t M, int64_t N, int64_t slabs, int64_t splits, int64_t extra) {
-  const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256) * splits;
+int64_t wide_time(int64_t M, int64_t cols, int64_t slabs, int64_t splits, int64_t extra) {
+  const int64_t tiles = ((M + 255) / 256) * cols * splits;
   const int64_t round = slabs * 1290 + 8000 + extra;
   return 4000 + tiles / 256 * round + (tiles % 256 ? round * 85 / 100 : 0);
 }
-// Whether the 256 x 256 kernel serves a product: B parts that never split a
-// tile, and the smaller modelled time.  Measured, 128 x 128 -> 256 x 256:
+// Whether the 256 x 256 kernel serves a product.  Measured, 128 x 128 -> 256 x 256:
 // M = 16384, N = 3072, K = 1024 117 -> 91 us (1.13 PFLOP/s); 1024 x 3072
 // 101 -> 74 us (1.39); M = 65536, N = K = 768 89 -> 76 us; but M = 8192,
 // N = 2304, K = 768 (1.1 rounds) 38.7 -> 44.8 us: it stays on 128 x 128.
 bool wide_ok(const GemmDesc& g, int64_t kchunk, int64_t splits, EpiCost c) {
-  if (g.seg == kSegN && g.seg_len % 256 != 0) return false;
-  return wide_time(g.M, g.N, kchunk / 64, splits, c.wide) <
-         pipe_time(g.M, g.N, kchunk / 64, splits, c.pipe);
+  return wide_time(g.M, col_tiles(g, 256), kchunk / 64, splits, c.wide) <
+         pipe_time(g.M, col_tiles(g, 128), kchunk / 64, splits, c.pipe);
 }
 
 template <bool AMC, bool BNC, int SEG, class Epi>
@@ -1720,12 +1450,21 @@ hipError_t launch_wide(const GemmDesc& g, const Epi& epi, hipStream_t s) {
   kchunk = (kchunk + 63) / 64 * 64;
   if (g.kchunk > 0) kchunk = g.kchunk;
   splits = (g.K + kchunk - 1) / kchunk;
-  dim3 grid((g.N + 255) / 256, (g.M + 255) / 256, splits);
+  dim3 grid((unsigned)col_tiles(g, 256), (g.M + 255) / 256, splits);
   const int group = xcd_group_rows((int)grid.x, (int)grid.y, (int)grid.z);
   hipLaunchKernelGGL((gemm_wide_kernel<AMC, BNC, SEG, Epi>), grid, dim3(256), 0, s, g.M, g.N, g.K,
                      A, B, kchunk, group, epi);
   return hipGetLastError();
 }
+
+// Up to this many 128 x 128 tiles (half the CUs) a product runs on 32 x 128
+// tiles, four workgroups for one, with four slabs in flight: it is bound by
+// the latency of its slabs, not by their number.  Measured, 128 x 128 ->
+// 32 x 128: M = 700, N = K = 768 (36 tiles) 10.5 -> 7.2 us, N = 768, K = 2304
+// 21 -> 13 us; M = 2000, N = K = 256 6.0 -> 4.3 us; M = 8192, N = 256, K = 768
+// (128 tiles) 10.0 -> 9.2 us; M = 1000, N = 2304, K = 768 (144) 11.4 -> 14.4.
+// (64 x 128 tiles were never the fastest.)
+constexpr int64_t kSmallTiles = 128;
 
 template <bool AMC, bool BNC, int SEG, class Epi>
 hipError_t launch_pipe(const GemmDesc& g, const Epi& epi, hipStream_t s) {
@@ -1738,23 +1477,29 @@ hipError_t launch_pipe(const GemmDesc& g, const Epi& epi, hipStream_t s) {
     int splits = g.splits < 1 ? 1 : g.splits;
     if (g.kchunk > 0) splits = (g.K + g.kchunk - 1) / g.kchunk;
     const int64_t wgs = (int64_t)((g.N + 127) / 128) * ((g.M + 127) / 128) * splits;
-    if (wgs >= 256) return launch_pipe_w<2, 2, AMC, BNC, SEG>(g, epi, s);
+    if (wgs >= 256) return launch_pipe_w<128, 2, 2, 2, AMC, BNC, SEG>(g, epi, s);
+  } else {
+    const int sp = g.splits < 1 ? 1 : g.splits;
+    const int splits = g.kchunk > 0 ? (g.K + g.kchunk - 1) / g.kchunk : sp;
+    const int64_t tiles = col_tiles(g, 128) * ((g.M + 127) / 128) * splits;
+    if (tiles <= kSmallTiles) return launch_pipe_w<32, 4, 1, 4, AMC, BNC, SEG>(g, epi, s);
   }
-  if constexpr (SEG == kSegK) return launch_pipe_w<2, 2, AMC, BNC, SEG>(g, epi, s);
-  return launch_pipe_w<2, 4, AMC, BNC, SEG>(g, epi, s);
+  if constexpr (SEG == kSegK) return launch_pipe_w<128, 2, 2, 2, AMC, BNC, SEG>(g, epi, s);
+  return launch_pipe_w<128, 2, 2, 4, AMC, BNC, SEG>(g, epi, s);
 }
 
+// The bf16 kernels need whole 64-deep slabs unless both operands are
+// row-contiguous, row-contiguous operands of at least 8 rows, and parts
+// split along K never split a slab; every product of the layer (D a multiple
+// of 64) is of that kind.
 template <typename T, bool AMC, bool BNC, int SEG, class Epi>
 hipError_t launch_any(const GemmDesc& g, const Epi& epi, hipStream_t s) {
   if constexpr (sizeof(T) == 4) return launch_f32<AMC, BNC, SEG>(g, epi, s);
   if constexpr (sizeof(T) == 2) {
-    // The pipelined kernel needs whole 64-deep slabs, operands of at least
-    // 8 rows, and B parts that never split a tile (N) or a slab (K).
-    bool ok = g.K % 64 == 0 && g.M >= 8 && g.N >= 8;
-    if (SEG == kSegN) ok = ok && g.seg_len % 128 == 0;
-    if (SEG == kSegK) ok = ok && g.seg_len % 64 == 0;
-    if (ok) return launch_pipe<AMC, BNC, SEG>(g, epi, s);
-    return launch<T, AMC, BNC, SEG>(g, epi, s);
+    if (!(AMC && BNC) && g.K % 64 != 0) return hipErrorInvalidValue;
+    if ((AMC && g.M < 8) || g.N < 8) return hipErrorInvalidValue;
+    if (SEG != kSegNone && g.seg_len % 64 != 0) return hipErrorInvalidValue;
+    return launch_pipe<AMC, BNC, SEG>(g, epi, s);
   }
 }
 
@@ -1797,7 +1542,7 @@ static int splitk_plan(bool bf, int M, int N, int K, int min_k, int* kchunk) {
   if (sp < 1) sp = 1;
   int kc = (K + sp - 1) / sp;
   kc = (kc + 63) / 64 * 64;
-  if (bf && K >= kWideSplitK && K % 64 == 0) {
+  if (bf && K >= kWideSplitK) {
     const int t256 = ((M + 255) / 256) * ((N + 255) / 256);
     int sw = 256 / t256;
     if (sw < 1) sw = 1;
@@ -1805,7 +1550,8 @@ static int splitk_plan(bool bf, int M, int N, int K, int min_k, int* kchunk) {
     sw = (K + kw - 1) / kw;
     // plus the partial tiles, written and read back at about 4 TB/s
     const int64_t sn = (K + kc - 1) / kc, part = (int64_t)M * N * 8 / 4000;
-    if (wide_time(M, N, kw / 64, sw, 0) + part * sw < pipe_time(M, N, kc / 64, sn, 0) + part * sn)
+    if (wide_time(M, (N + 255) / 256, kw / 64, sw, 0) + part * sw <
+        pipe_time(M, (N + 127) / 128, kc / 64, sn, 0) + part * sn)
       kc = kw;
   }
   *kchunk = kc;
@@ -1818,14 +1564,6 @@ struct EpiSegOut {
   int64_t ldc;
   int seg;
   int accumulate;
-  __device__ __forceinline__ void operator()(int m, int n, f32x4 v) const {
-    const int sg = n / seg;
-    float* base = C[sg];
-    if (!base) return;
-    f32x4* dst = reinterpret_cast<f32x4*>(base + (int64_t)m * ldc + (n - sg * seg));
-    if (accumulate) v += *dst;
-    *dst = v;
-  }
   // (Output segments are multiples of 8 columns wide, so 8 columns never
   // straddle two of them.)
   __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {

@@ -126,8 +126,10 @@ typedef struct {
  * it had run on `stream`.  The caller creates and owns the stream (same
  * device as `stream`, default priority) and the two events (timing may be
  * disabled), and must not use one bcmt_side in two calls that enqueue at the
- * same time.  Passing NULL runs everything on `stream`.  While stage tracing
- * is on, the second stream is not used. */
+ * same time.  Passing NULL runs everything on `stream`, and so does a pass
+ * too small to gain from the second stream (the events cost the host more
+ * than its products take).  While stage tracing is on, the second stream is
+ * not used. */
 typedef struct {
   void* stream; /* hipStream_t */
   void* fork;   /* hipEvent_t, recorded on `stream` before each branch */

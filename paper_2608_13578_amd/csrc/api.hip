@@ -587,7 +587,8 @@ static int layer_forward(const bcmt_config* cfg, const void* X, const bcmt_param
 static int layer_backward(const bcmt_config* cfg, const void* X, const bcmt_params* prm,
                           const void* saved, const void* dY, void* dX, const bcmt_grads* grads,
                           void* ws, size_t ws_bytes, void* stream, const bcmt_side* side,
-                          bool chunk, const bcmt_carry* dcout, const bcmt_carry* dcin) {
+                          bool chunk, const bcmt_carry* dcout, const bcmt_carry* dcin,
+                          bool fork_small = false) {
   int st = check_config(cfg);
   if (st != BCMT_OK) return st;
   if (!X || !prm || !saved || !dY) return BCMT_ERR_INVALID;
@@ -618,9 +619,21 @@ static int layer_backward(const bcmt_config* cfg, const void* X, const bcmt_para
   if (ws_bytes < p.bwd_bytes) return BCMT_ERR_WORKSPACE;
 
   // The weight-gradient products go to the caller's second stream when one
-  // is given.  With per-stage tracing on, everything runs on the caller's
-  // stream so that each stage is timed alone.
-  const bool fork = side && !g_trace.on.load(std::memory_order_relaxed);
+  // is given and they are worth it: the three forks and the join cost the
+  // host about 50 us (each an event record and a wait), more than a small
+  // pass takes on the GPU.  Measured, second stream against one stream, the
+  // step forward + backward: B T = 256, D = 128 f32 180 against 131 us;
+  // B T = 2000, D = 256 166 against 122; B T = 16384, D = 128 177 against 153;
+  // at B T D^2 = 2.7e8 (1024 x 512) 173 against 139, but B T = 2048, D = 768
+  // 176 against 192.  float32 products are ten times slower: 1024 x 256 168
+  // against 170, 2048 x 256 180 against 187.  Inside a model step
+  // (fork_small) the host is far ahead, and small layers fork too (the step
+  // of the 6-layer model at D = 128: 3.40 against 3.47 ms).  With per-stage
+  // tracing on, everything runs on the caller's stream so that each stage is
+  // timed alone.
+  const double work = (double)p.B * p.T * p.D * p.D;
+  const bool worth = fork_small || work >= (p.dt == DType::BF16 ? 3e8 : 6e7);
+  const bool fork = side && worth && !g_trace.on.load(std::memory_order_relaxed);
   const hipStream_t main_s = (hipStream_t)stream;
   const hipStream_t side_s = fork ? (hipStream_t)side->stream : main_s;
   const hipEvent_t ev_fork = fork ? (hipEvent_t)side->fork : nullptr;
@@ -819,6 +832,16 @@ static int layer_backward(const bcmt_config* cfg, const void* X, const bcmt_para
 #undef SIDE_END
   return BCMT_OK;
 }
+
+// The layer's backward as a part of a model step (model.hip).
+namespace bcmt {
+int layer_backward_in_model(const bcmt_config* cfg, const void* X, const bcmt_params* prm,
+                            const void* saved, const void* dY, void* dX, const bcmt_grads* grads,
+                            void* ws, size_t ws_bytes, void* stream, const bcmt_side* side) {
+  return layer_backward(cfg, X, prm, saved, dY, dX, grads, ws, ws_bytes, stream, side, false,
+                        nullptr, nullptr, true);
+}
+}  // namespace bcmt
 
 // ------------------------------------------------------------------ allocation-free forward
 // The forward pass's workspace for bcmt_layer_forward_noalloc: one array per

@@ -21,6 +21,9 @@
 #include "kernels.h"
 
 namespace bcmt {
+int layer_backward_in_model(const bcmt_config* cfg, const void* X, const bcmt_params* prm,
+                            const void* saved, const void* dY, void* dX, const bcmt_grads* grads,
+                            void* ws, size_t ws_bytes, void* stream, const bcmt_side* side);
 namespace {
 
 constexpr float kLnEps = 1e-5f;
@@ -659,7 +662,7 @@ int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
     lg.dWm = gw(lidx(l, 6));
     lg.dWg = gw(lidx(l, 7));
     lg.dwp = gw(lidx(l, 8));
-    int e = bcmt_layer_backward(&p.lc, W + p.a + act * l, &lp, W + p.saved + p.layer_saved * l,
+    int e = layer_backward_in_model(&p.lc, W + p.a + act * l, &lp, W + p.saved + p.layer_saved * l,
                                 dr, W + p.dxm, &lg, W + p.lws, p.layer_ws, s, side);
     if (e != BCMT_OK) return e;
     CHK(ln_bwd((const bf16*)(W + p.dxm), R(2 * l), st1m(l), lidx(l, 0), dr, dr));

@@ -833,8 +833,10 @@ static int layer_backward(const bcmt_config* cfg, const void* X, const bcmt_para
   return BCMT_OK;
 }
 
-// The layer's backward as a part of a model step (model.hip).
+// The layer's backward as a part of a model step, and whether stage tracing
+// is on (model.hip).
 namespace bcmt {
+bool trace_is_on() { return g_trace.on.load(std::memory_order_relaxed); }
 int layer_backward_in_model(const bcmt_config* cfg, const void* X, const bcmt_params* prm,
                             const void* saved, const void* dY, void* dX, const bcmt_grads* grads,
                             void* ws, size_t ws_bytes, void* stream, const bcmt_side* side) {

@@ -24,6 +24,7 @@ namespace bcmt {
 int layer_backward_in_model(const bcmt_config* cfg, const void* X, const bcmt_params* prm,
                             const void* saved, const void* dY, void* dX, const bcmt_grads* grads,
                             void* ws, size_t ws_bytes, void* stream, const bcmt_side* side);
+bool trace_is_on();
 namespace {
 
 constexpr float kLnEps = 1e-5f;
@@ -189,28 +190,185 @@ __global__ __launch_bounds__(1024) void ln_bwd_kernel(
   }
 }
 
+// The two LayerNorm kernels for widths of 8 LPR columns, LPR a power of two
+// up to 64: LPR lanes take a row, 16 bytes each, so that a wave has 64 / LPR
+// rows and every load is a full vector.  Bound by latency and bandwidth; at
+// B T = 16384, d = 128 the two-byte loads of the kernels above (one row per
+// wave, which serve the other widths) took 8.4 us forward and 11.7 us
+// backward for the 12 and 17 MB they move; these take 4.6 and 8.5.
+template <int LPR>
+__device__ __forceinline__ float row_sum(float v) {
+#pragma unroll
+  for (int m = 1; m < LPR; m *= 2) v += __shfl_xor(v, m);
+  return v;
+}
+
+// The forward adds in the order of add_ln_fwd_kernel (columns l and l + 64 of
+// a row first, then over l in pairs, quads, ...), so that the loss does not
+// depend on which of the two ran; that takes at most two columns per l.
+template <int LPR>
+__global__ __launch_bounds__(256) void add_ln_fwd_vec_kernel(
+    const bf16* __restrict__ x, const bf16* __restrict__ y, bf16* __restrict__ xs,
+    const float* __restrict__ g, const float* __restrict__ b, bf16* __restrict__ out,
+    float* __restrict__ mean, float* __restrict__ rstd, int rows) {
+  static_assert(LPR == 8 || LPR == 16, "one or two 64-column groups");
+  constexpr int d = 8 * LPR, RPG = 256 / LPR;  // rows per workgroup
+  const int r = blockIdx.x * RPG + threadIdx.x / LPR, q = threadIdx.x % LPR, c = q * 8;
+  const bool on = r < rows;
+  const int64_t at = (int64_t)(on ? r : rows - 1) * d + c;
+  float v[8], gg[8], bb[8];
+  ld8(x + at, v);
+  ld8(g + c, gg);
+  ld8(b + c, bb);
+  if (y) {
+    float w[8];
+    ld8(y + at, w);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = (float)(bf16)(v[e] + w[e]);
+    if (on) st8(xs + at, v);
+  }
+  // lo, hi: columns l and l + 64 of this lane's eight l (8 lanes cover them)
+  float lo[8], hi[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float o = LPR == 16 ? __shfl_xor(v[e], 8) : 0.f;
+    lo[e] = q < 8 ? v[e] : o;
+    hi[e] = q < 8 ? o : v[e];
+  }
+  auto total = [](const float(&t)[8]) {
+    float s = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+    s += __shfl_xor(s, 1);
+    s += __shfl_xor(s, 2);
+    return s + __shfl_xor(s, 4);
+  };
+  float t[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) t[e] = LPR == 16 ? lo[e] + hi[e] : lo[e];
+  const float mu = total(t) / (float)d;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float a = lo[e] - mu, h = hi[e] - mu;
+    t[e] = LPR == 16 ? fmaf(h, h, a * a) : a * a;
+  }
+  const float rs = rsqrtf(total(t) / (float)d + kLnEps);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = (v[e] - mu) * rs * gg[e] + bb[e];
+  if (!on) return;
+  st8(out + at, v);
+  if (q == 0) {
+    mean[r] = mu;
+    rstd[r] = rs;
+  }
+}
+
+// As ln_bwd_kernel: kLnRowsPerGroup rows per workgroup and one pair of
+// partial rows of the gain and bias gradients.
+template <typename TY, int LPR>
+__global__ __launch_bounds__(256) void ln_bwd_vec_kernel(
+    const TY* __restrict__ dy, const bf16* __restrict__ xs, const float* __restrict__ mean,
+    const float* __restrict__ rstd, const float* __restrict__ g, const bf16* dres, bf16* dx,
+    float* __restrict__ part, int rows) {
+  constexpr int d = 8 * LPR, RPI = 256 / LPR;     // rows at a time
+  constexpr int NI = kLnRowsPerGroup / RPI;       // times
+  constexpr int U = NI < 4 ? NI : 4;              // of which in flight together
+  static_assert(NI % U == 0, "row batches");
+  __shared__ float red[RPI][2][d];
+  const int rl = threadIdx.x / LPR, c = threadIdx.x % LPR * 8;
+  float gg[8], pg[8], pb[8];
+  ld8(g + c, gg);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) pg[e] = pb[e] = 0.f;
+  const int r0 = blockIdx.x * kLnRowsPerGroup + rl;
+#pragma unroll 1
+  for (int i0 = 0; i0 < NI; i0 += U) {
+    float dv[U][8], xh[U][8], dr[U][8], mu[U], rs[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = min(r0 + (i0 + u) * RPI, rows - 1);
+      const int64_t at = (int64_t)r * d + c;
+      ld8(dy + at, dv[u]);
+      ld8(xs + at, xh[u]);
+      if (dres) {
+        ld8(dres + at, dr[u]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) dr[u][e] = 0.f;
+      }
+      mu[u] = mean[r];
+      rs[u] = rstd[r];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int r = r0 + (i0 + u) * RPI;
+      const bool on = r < rows;
+      float gy[8], s1 = 0.f, s2 = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        xh[u][e] = (xh[u][e] - mu[u]) * rs[u];
+        gy[e] = dv[u][e] * gg[e];
+        s1 += gy[e];
+        s2 += gy[e] * xh[u][e];
+        if (on) {
+          pg[e] += dv[u][e] * xh[u][e];
+          pb[e] += dv[u][e];
+        }
+      }
+      const float m1 = row_sum<LPR>(s1) / (float)d, m2 = row_sum<LPR>(s2) / (float)d;
+      float o[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] = rs[u] * (gy[e] - m1 - xh[u][e] * m2) + dr[u][e];
+      if (on) st8(dx + (int64_t)r * d + c, o);
+    }
+  }
+  st8(&red[rl][0][c], pg);
+  st8(&red[rl][1][c], pb);
+  __syncthreads();
+  for (int k = threadIdx.x; k < 2 * d; k += 256) {
+    const float* q = &red[0][0][0] + k;
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < RPI; ++w) t += q[w * 2 * d];
+    part[(int64_t)blockIdx.x * 2 * d + k] = t;
+  }
+}
+
+// Gain and bias gradients of every LayerNorm of the model, in one launch at
+// the end (one launch per LayerNorm was 13 of 7.3 us each, with four
+// workgroups): LayerNorm q = blockIdx.y has its parts at part + q parts 2 d and
+// its gradients [dg | db] (2 d) at grads + off, where the 2 n of the layers
+// alternate between two offsets a layer apart and the last is the final one.
 // dg[c] = sum_w part[w][0][c], db[c] = sum_w part[w][1][c] in a fixed
 // order: workgroup = 64 columns of one of the two, wave k of 16 sums the
 // parts k, k + 16, ... (four accumulators in turn), then the waves add up.
-__global__ __launch_bounds__(1024) void ln_param_grad_kernel(const float* __restrict__ part,
+struct LnGradAt {
+  int64_t first, second, layer, last;
+};
+__global__ __launch_bounds__(1024) void ln_param_grad_kernel(const float* __restrict__ part0,
                                                              int nparts, int d,
-                                                             float* __restrict__ dg,
-                                                             float* __restrict__ db) {
+                                                             float* __restrict__ grads,
+                                                             LnGradAt at) {
   __shared__ float red[16][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int c0 = blockIdx.x * 64;  // over the 2 d columns of [dg | db]
-  const int which = c0 / d, col = c0 % d + lane;
-  const float* src = part + (int64_t)which * d + col;
+  const int q = blockIdx.y;
+  const int64_t off = q + 1 == (int)gridDim.y ? at.last
+                                              : (q & 1 ? at.second : at.first) + (q >> 1) * at.layer;
+  const int col = blockIdx.x * 64 + lane;  // over the 2 d columns of [dg | db]
+  const float* src = part0 + (int64_t)q * nparts * 2 * d + col;
   float acc[4] = {0.f, 0.f, 0.f, 0.f};
-  int k = 0;
-  for (int w = wave; w < nparts; w += 16, ++k) acc[k & 3] += src[(int64_t)w * 2 * d];
+  for (int w = wave; w < nparts; w += 64) {
+    float t[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = w + 16 * u < nparts ? src[(int64_t)(w + 16 * u) * 2 * d] : 0.f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) acc[u] += t[u];
+  }
   red[wave][lane] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
   __syncthreads();
   if (wave == 0) {
     float t = 0.f;
 #pragma unroll
     for (int w = 0; w < 16; ++w) t += red[w][lane];
-    (which == 0 ? dg : db)[col] = t;
+    grads[off + col] = t;
   }
 }
 
@@ -270,22 +428,69 @@ __global__ __launch_bounds__(1024) void loss_sum_kernel(const float* __restrict_
   }
 }
 
-// dE[tok[r]] += dx[r] (float32 atomics: rows sharing a token add in any
-// order), 8 columns per thread.
-__global__ __launch_bounds__(256) void embed_bwd_kernel(const int32_t* __restrict__ tok,
-                                                        const bf16* __restrict__ dx,
-                                                        float* __restrict__ dE, int rows, int d,
-                                                        int V) {
-  const int per = d / 8;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (int64_t)rows * per) return;
-  const int r = (int)(i / per), c = (int)(i % per) * 8;
-  const int tk = min(max(tok[r], 0), V - 1);
-  float v[8];
-  ld8(dx + (int64_t)r * d + c, v);
-  float* dst = dE + (int64_t)tk * d + c;
+// dE[tok[r]] += dx[r].  Text repeats its tokens (the most frequent one may be
+// every tenth), and adding every row with atomics queues hundreds of them on
+// the same addresses: 236 us at 16384 rows of 128 with the frequencies of
+// text.  A workgroup takes 256 rows and 32 columns, orders the rows by token
+// in LDS (a thread counts the keys below its own), and each half-wave adds
+// up the rows of a token in order, one column a lane, so that the sum's
+// float32 atomics are one 128-byte line a token: 22 us (workgroups add in any
+// order; four lanes of eight columns a token took 64, bound by 32-byte atomics).
+constexpr int kEbRows = 256, kEbCols = 32, kEbThreads = 1024;
+__global__ __launch_bounds__(kEbThreads) void embed_bwd_kernel(const int32_t* __restrict__ tok,
+                                                               const bf16* __restrict__ dx,
+                                                               float* __restrict__ dE, int rows,
+                                                               int d, int V) {
+  __shared__ __attribute__((aligned(16))) int key[kEbRows];
+  __shared__ int sorted[kEbRows];
+  __shared__ short order[kEbRows], start[kEbRows + 1];
+  __shared__ int heads[kEbRows / 64];
+  const int tid = threadIdx.x, r0 = blockIdx.x * kEbRows, n = min(kEbRows, rows - r0);
+  const int wave = tid >> 6, lane = tid & 63;
+  const bool sorts = tid < kEbRows;
+  int k = 0x7fffffff;
+  if (tid < n) k = min(max(tok[r0 + tid], 0), V - 1);
+  if (sorts) key[tid] = k;
+  __syncthreads();
+  if (sorts) {
+    int rank = 0;
+    for (int j = 0; j < kEbRows; j += 4) {
+      const int4 q = *reinterpret_cast<const int4*>(key + j);
+      rank += (q.x < k || (q.x == k && j < tid)) + (q.y < k || (q.y == k && j + 1 < tid)) +
+              (q.z < k || (q.z == k && j + 2 < tid)) + (q.w < k || (q.w == k && j + 3 < tid));
+    }
+    sorted[rank] = k;
+    order[rank] = (short)tid;
+  }
+  __syncthreads();
+  // the first row of every token, compacted
+  const bool head = tid < n && (tid == 0 || sorted[tid] != sorted[tid - 1]);
+  const uint64_t bal = __ballot(head);
+  if (sorts && lane == 0) heads[wave] = __popcll(bal);
+  __syncthreads();
+  int before = 0, nseg = 0;
 #pragma unroll
-  for (int k = 0; k < 8; ++k) unsafeAtomicAdd(dst + k, v[k]);
+  for (int w = 0; w < kEbRows / 64; ++w) {
+    if (w < wave) before += heads[w];
+    nseg += heads[w];
+  }
+  if (head) start[before + __popcll(bal & ((1ull << lane) - 1))] = (short)tid;
+  if (tid == 0) start[nseg] = (short)n;
+  __syncthreads();
+  const int c = blockIdx.y * kEbCols + (tid & 31);
+  for (int sgm = tid >> 5; sgm < nseg; sgm += kEbThreads / 32) {
+    const int a = start[sgm], e = start[sgm + 1];
+    float acc = 0.f;
+    for (int i = a; i < e; i += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        v[u] = i + u < e ? (float)dx[(int64_t)(r0 + order[min(i + u, e - 1)]) * d + c] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += v[u];
+    }
+    unsafeAtomicAdd(dE + (int64_t)sorted[a] * d + c, acc);
+  }
 }
 
 // dPe[t] = sum_b dx[b T + t], fixed order.
@@ -374,7 +579,7 @@ struct ModelPlan {
   size_t layer_saved, layer_ws, wpart_bytes, nparts;
   // offsets into the workspace
   size_t r, a, st1, saved, y, bn, st2, U, A, f, stf, logits, hpart, lse, row_loss;
-  size_t dr, dt, df32, dU, dxm, lnpart, wpart, lws, total;
+  size_t dr, dr2, dt, df32, dU, dxm, lnpart, wpart, lws, total;
 
   explicit ModelPlan(const bcmt_model_config& c) {
     BT = c.B * c.T;
@@ -418,12 +623,13 @@ struct ModelPlan {
     hpart = take((size_t)BT * (Vp / 128) * 8);
     lse = take(rowf);
     row_loss = take(rowf);
-    dr = take(act);               // gradient of the residual stream
+    dr = take(act);               // gradient of the residual stream above a layer's MLP
+    dr2 = take(act);              // and between its MLP and its mixing layer
     dt = take(act);
     df32 = take((size_t)BT * d * 4);  // the head's input gradient (float32)
     dU = take(act4);
     dxm = take(act);
-    lnpart = take(nparts * 2 * d * 4);
+    lnpart = take((2 * n + 1) * nparts * 2 * d * 4);  // one set per LayerNorm
     wpart = take(wpart_bytes);
     lws = take(layer_ws);
     total = off;
@@ -519,8 +725,23 @@ int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
     if (hipGetLastError() != hipSuccess) return BCMT_ERR_HIP; \
   } while (0)
   // (The LayerNorm gains and biases are read in float32 from `params`.)
-  const unsigned ln_grid = (BT + 3) / 4;
   const unsigned ew_grid = blocks_for((int64_t)BT * (d / 8), 256, 1 << 30);
+
+  auto add_ln = [&](const bf16* x, const bf16* y, bf16* xs, int gi, bf16* out,
+                    float* stats) -> hipError_t {
+    const float *g = pf(gi), *b = pf(gi + 1);
+    float* rs = stats + rowf / 4;
+#define LN_VEC(LPR)                                                                          \
+  hipLaunchKernelGGL(add_ln_fwd_vec_kernel<LPR>, dim3((BT + 256 / LPR - 1) / (256 / LPR)),   \
+                     dim3(256), 0, s, x, y, xs, g, b, out, stats, rs, BT)
+    if (d == 64) LN_VEC(8);
+    else if (d == 128) LN_VEC(16);
+    else
+      hipLaunchKernelGGL(add_ln_fwd_kernel, dim3((BT + 3) / 4), dim3(256), 0, s, x, y, xs, g, b,
+                         out, stats, rs, BT, d);
+#undef LN_VEC
+    return hipGetLastError();
+  };
 
   // ---- forward
   hipLaunchKernelGGL(embed_fwd_kernel, dim3(ew_grid), dim3(256), 0, s, tokens, pw(0), pw(1), R(0),
@@ -528,20 +749,14 @@ int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
   KCHK();
   for (int l = 0; l < n; ++l) {
     bf16* a = (bf16*)(W + p.a + act * l);
-    hipLaunchKernelGGL(add_ln_fwd_kernel, dim3(ln_grid), dim3(256), 0, s, R(2 * l), nullptr,
-                       nullptr, pf(lidx(l, 0)), pf(lidx(l, 1)), a, st1m(l), st1m(l) + rowf / 4,
-                       BT, d);
-    KCHK();
+    CHK(add_ln(R(2 * l), nullptr, nullptr, lidx(l, 0), a, st1m(l)));
     const bcmt_params lp{pw(lidx(l, 2)), pw(lidx(l, 3)), pw(lidx(l, 4)), pw(lidx(l, 5)),
                          pw(lidx(l, 6)), pw(lidx(l, 7)), pw(lidx(l, 8)), nullptr};
     int e = bcmt_layer_forward(&p.lc, a, &lp, W + p.y, W + p.saved + p.layer_saved * l,
                                W + p.lws, p.layer_ws, s);
     if (e != BCMT_OK) return e;
     bf16* bn = (bf16*)(W + p.bn + act * l);
-    hipLaunchKernelGGL(add_ln_fwd_kernel, dim3(ln_grid), dim3(256), 0, s, R(2 * l),
-                       (const bf16*)(W + p.y), R(2 * l + 1), pf(lidx(l, 9)), pf(lidx(l, 10)), bn,
-                       st2m(l), st2m(l) + rowf / 4, BT, d);
-    KCHK();
+    CHK(add_ln(R(2 * l), (const bf16*)(W + p.y), R(2 * l + 1), lidx(l, 9), bn, st2m(l)));
     bf16* U = (bf16*)(W + p.U + act4 * l);
     bf16* A = (bf16*)(W + p.A + act4 * l);
     {
@@ -557,9 +772,7 @@ int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
   }
   const int lf = 2 + kLayerArrays * n;
   float* stf = (float*)(W + p.stf);
-  hipLaunchKernelGGL(add_ln_fwd_kernel, dim3(ln_grid), dim3(256), 0, s, R(2 * n), nullptr, nullptr,
-                     pf(lf), pf(lf + 1), (bf16*)(W + p.f), stf, stf + rowf / 4, BT, d);
-  KCHK();
+  CHK(add_ln(R(2 * n), nullptr, nullptr, lf, (bf16*)(W + p.f), stf));
   bf16* logits = (bf16*)(W + p.logits);
   float* lse = (float*)(W + p.lse);
   // logits = f E^T: B[k][v] = E[v][k], K-contiguous.  The product is taken
@@ -582,25 +795,36 @@ int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
   KCHK();
 
   // ---- backward
+  // (the second stream as in the layer's backward: not while tracing)
+  const bool fork = side && !trace_is_on();
+  const hipStream_t side_s = fork ? (hipStream_t)side->stream : s;
   float* wpart = (float*)(W + p.wpart);
-  float* lnpart = (float*)(W + p.lnpart);
   bf16* dr = (bf16*)(W + p.dr);
+  bf16* dr2 = (bf16*)(W + p.dr2);
   bf16* dt = (bf16*)(W + p.dt);
-  auto ln_bwd = [&](auto dy, const bf16* xs, const float* stats, int gi, const bf16* dres,
+  // LayerNorm q's backward (its gain is array gi); the gain and bias
+  // gradients of all of them are summed at the end.
+  auto ln_bwd = [&](int q, auto dy, const bf16* xs, const float* stats, int gi, const bf16* dres,
                     bf16* dx) -> hipError_t {
     using TY = typename std::remove_cv<typename std::remove_pointer<decltype(dy)>::type>::type;
+    float* part = (float*)(W + p.lnpart) + (size_t)q * p.nparts * 2 * d;
+    const float* rs = stats + rowf / 4;
+    const dim3 grid((unsigned)p.nparts);
+#define LN_VEC(LPR)                                                                             \
+  hipLaunchKernelGGL((ln_bwd_vec_kernel<TY, LPR>), grid, dim3(256), 0, s, dy, xs, stats, rs,    \
+                     pf(gi), dres, dx, part, BT)
     const size_t lds = (size_t)kLnWaves * 2 * d * sizeof(float);
-    if (d <= 256)
-      hipLaunchKernelGGL((ln_bwd_kernel<TY, 4, 4>), dim3((unsigned)p.nparts), dim3(64 * kLnWaves),
-                         lds, s, dy, xs, stats, stats + rowf / 4, pf(gi), dres, dx, lnpart, BT, d);
+    if (d == 64) LN_VEC(8);
+    else if (d == 128) LN_VEC(16);
+    else if (d == 256) LN_VEC(32);
+    else if (d == 512) LN_VEC(64);
+    else if (d < 256)
+      hipLaunchKernelGGL((ln_bwd_kernel<TY, 4, 4>), grid, dim3(64 * kLnWaves), lds, s, dy, xs,
+                         stats, rs, pf(gi), dres, dx, part, BT, d);
     else
-      hipLaunchKernelGGL((ln_bwd_kernel<TY, 16, 1>), dim3((unsigned)p.nparts),
-                         dim3(64 * kLnWaves), lds, s, dy, xs, stats, stats + rowf / 4, pf(gi),
-                         dres, dx, lnpart, BT, d);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(ln_param_grad_kernel, dim3(2 * d / 64), dim3(1024), 0, s, lnpart,
-                       (int)p.nparts, d, gw(gi), gw(gi + 1));
+      hipLaunchKernelGGL((ln_bwd_kernel<TY, 16, 1>), grid, dim3(64 * kLnWaves), lds, s, dy, xs,
+                         stats, rs, pf(gi), dres, dx, part, BT, d);
+#undef LN_VEC
     return hipGetLastError();
   };
   // dlogits = (softmax - onehot) / (B T), over the logits buffer
@@ -622,7 +846,7 @@ int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
     CHK(gemm_splitk(DType::BF16, g, wpart, (float*)(W + p.df32), nullptr, nullptr, d, d, false,
                     kDfMinK, s));
   }
-  CHK(ln_bwd((const float*)(W + p.df32), R(2 * n), stf, lf, nullptr, dr));
+  CHK(ln_bwd(2 * n, (const float*)(W + p.df32), R(2 * n), stf, lf, nullptr, dr));
   for (int l = n - 1; l >= 0; --l) {
     const bf16* U = (const bf16*)(W + p.U + act4 * l);
     const bf16* A = (const bf16*)(W + p.A + act4 * l);
@@ -634,15 +858,24 @@ int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
                  kSegNone, 0, 1};
       CHK(gemm_gelu_bwd(DType::BF16, g, U, dU, 4 * d, s));
     }
+    // The MLP's weight gradients, which nothing below reads, run on the second
+    // stream beside the LayerNorm and the mixing layer's backward; their
+    // inputs dr, dU, A and bn are not written before the join below (the
+    // LayerNorm's result goes to dr2).  At B T = 16384, d = 128 they are 40 us
+    // a layer of the critical path.
+    if (fork) {
+      CHK(hipEventRecord((hipEvent_t)side->fork, s));
+      CHK(hipStreamWaitEvent(side_s, (hipEvent_t)side->fork, 0));
+    }
     {
       GemmDesc g{4 * d, d, BT, A, 4 * d, true, {dr, nullptr, nullptr}, d, true, kSegNone, 0, 1};
       CHK(gemm_splitk(DType::BF16, g, wpart, gw(lidx(l, 12)), nullptr, nullptr, d, d, false,
-                      kWgradMinK, s));
+                      kWgradMinK, side_s));
     }
     {
       GemmDesc g{d, 4 * d, BT, bn, d, true, {dU, nullptr, nullptr}, 4 * d, true, kSegNone, 0, 1};
       CHK(gemm_splitk(DType::BF16, g, wpart, gw(lidx(l, 11)), nullptr, nullptr, 4 * d, 4 * d,
-                      false, kWgradMinK, s));
+                      false, kWgradMinK, side_s));
     }
     {
       // d(LN2 out) = dU W1^T: B[k][n] = W1[n][k], K-contiguous
@@ -650,7 +883,7 @@ int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
                  false, kSegNone, 0, 1};
       CHK(gemm_store(DType::BF16, g, dt, d, false, nullptr, 0, s));
     }
-    CHK(ln_bwd(dt, R(2 * l + 1), st2m(l), lidx(l, 9), dr, dr));
+    CHK(ln_bwd(2 * l + 1, dt, R(2 * l + 1), st2m(l), lidx(l, 9), dr, dr2));
     const bcmt_params lp{pw(lidx(l, 2)), pw(lidx(l, 3)), pw(lidx(l, 4)), pw(lidx(l, 5)),
                          pw(lidx(l, 6)), pw(lidx(l, 7)), pw(lidx(l, 8)), nullptr};
     bcmt_grads lg;
@@ -663,12 +896,24 @@ int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
     lg.dWg = gw(lidx(l, 7));
     lg.dwp = gw(lidx(l, 8));
     int e = layer_backward_in_model(&p.lc, W + p.a + act * l, &lp, W + p.saved + p.layer_saved * l,
-                                dr, W + p.dxm, &lg, W + p.lws, p.layer_ws, s, side);
+                                    dr2, W + p.dxm, &lg, W + p.lws, p.layer_ws, s, side);
     if (e != BCMT_OK) return e;
-    CHK(ln_bwd((const bf16*)(W + p.dxm), R(2 * l), st1m(l), lidx(l, 0), dr, dr));
+    if (fork) {
+      CHK(hipEventRecord((hipEvent_t)side->join, side_s));
+      CHK(hipStreamWaitEvent(s, (hipEvent_t)side->join, 0));
+    }
+    CHK(ln_bwd(2 * l, (const bf16*)(W + p.dxm), R(2 * l), st1m(l), lidx(l, 0), dr2, dr));
   }
-  hipLaunchKernelGGL(embed_bwd_kernel, dim3(ew_grid), dim3(256), 0, s, tokens, dr, gw(0), BT, d,
-                     c.V);
+  {
+    const LnGradAt at{(int64_t)array_offset(c, lidx(0, 0)), (int64_t)array_offset(c, lidx(0, 9)),
+                      (int64_t)(array_offset(c, lidx(1, 0)) - array_offset(c, lidx(0, 0))),
+                      (int64_t)array_offset(c, lf)};
+    hipLaunchKernelGGL(ln_param_grad_kernel, dim3(2 * d / 64, 2 * n + 1), dim3(1024), 0, s,
+                       (const float*)(W + p.lnpart), (int)p.nparts, d, grads, at);
+    KCHK();
+  }
+  hipLaunchKernelGGL(embed_bwd_kernel, dim3((BT + kEbRows - 1) / kEbRows, d / kEbCols),
+                     dim3(kEbThreads), 0, s, tokens, dr, gw(0), BT, d, c.V);
   KCHK();
   hipLaunchKernelGGL(pos_bwd_kernel, dim3(blocks_for((int64_t)c.T * d, 256, 1 << 30)), dim3(256),
                      0, s, dr, gw(1), c.B, c.T, d);

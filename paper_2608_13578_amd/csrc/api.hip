@@ -165,7 +165,7 @@ struct DecPlan {
   DType dt;
   size_t es;
   size_t Kc, Vc, Hc, spc, N, Z, C, state_bytes;
-  size_t o, Mt, part, cpart, ws_bytes;
+  size_t o, Mt, part, part2, cpart, ws_bytes;
 
   explicit DecPlan(const bcmt_config& c) {
     B = c.B;
@@ -193,6 +193,8 @@ struct DecPlan {
     o = take(BD * es);
     Mt = take(BD * es);
     part = take(dec_part_bytes(dt, B, D));
+    // the gate product's splits, formed while those of o Wo are still read
+    part2 = take(dt == DType::BF16 ? (size_t)dec_splits(dt, D, D, B) * B * D * 4 : 0);
     cpart = take(carry_part_bytes(B, D));
     ws_bytes = off;
   }
@@ -974,13 +976,21 @@ int bcmt_decode_step(const bcmt_config* cfg, const bcmt_params* prm, int64_t t, 
   LAUNCH(ST_DEC_ATTN, dec_attn(p.dt, part, ks3, S + p.Kc, S + p.Vc, W + p.o, p.B, D, p.H, p.L,
                                off, s));
   // h = o Wo (cached, with its pooling score), then the gate and injection.
+  // In bf16 the gate product forms h from the splits of o Wo itself.
   LAUNCH(ST_DEC_WO, dec_product(p.dt, W + p.o, D, prm->Wo, nullptr, nullptr, p.B, D, D, part, s));
-  LAUNCH(ST_DEC_WO_FIN, dec_wo_finish(p.dt, part, ks1, prm->wp, S + p.Hc, (float*)(S + p.spc),
-                                      p.B, D, p.L, off, s));
-  char* hrow = S + p.Hc + (size_t)off * D * p.es;
-  LAUNCH(ST_DEC_GATE, dec_product(p.dt, hrow, (int64_t)p.L * D, prm->Wg, nullptr, nullptr, p.B, D,
-                                  D, part, s));
-  LAUNCH(ST_DEC_GATE_FIN, dec_gate_finish(p.dt, part, ks1, S + p.Hc, (const float*)(S + p.C),
+  float* gpart = part;
+  if (p.dt == DType::BF16) {
+    gpart = (float*)(W + p.part2);
+    LAUNCH(ST_DEC_GATE, dec_finish_product(part, ks1, prm->wp, S + p.Hc, (float*)(S + p.spc),
+                                           prm->Wg, p.B, D, p.L, off, gpart, s));
+  } else {
+    LAUNCH(ST_DEC_WO_FIN, dec_wo_finish(part, ks1, prm->wp, S + p.Hc, (float*)(S + p.spc), p.B, D,
+                                        p.L, off, s));
+    char* hrow = S + p.Hc + (size_t)off * D * p.es;
+    LAUNCH(ST_DEC_GATE, dec_product(p.dt, hrow, (int64_t)p.L * D, prm->Wg, nullptr, nullptr, p.B,
+                                    D, D, part, s));
+  }
+  LAUNCH(ST_DEC_GATE_FIN, dec_gate_finish(p.dt, gpart, ks1, S + p.Hc, (const float*)(S + p.C),
                                           (cfg->flags & BCMT_FLAG_RESIDUAL) ? x : nullptr, y, p.B,
                                           D, p.L, off, s));
   if (off == p.L - 1) {

@@ -22,6 +22,9 @@
 // the step's epilogue (for the QKV product the attention kernel does it).
 // The kernel boundary makes the partials visible across the chip's L2s, so
 // nothing synchronises inside a kernel, and every run gives the same result.
+// In bf16 the products run on the matrix cores, 128 columns x 128 rows a
+// workgroup, and the gate product adds up the splits of o Wo itself (five
+// launches a token; float32 takes six).
 #include <hip/hip_runtime.h>
 
 #include <stdint.h>
@@ -171,23 +174,145 @@ __global__ __launch_bounds__(256) void dec_gemv_part_kernel(const T* __restrict_
 }
 
 // Sum of the K splits of output (b, n), in split order; eight splits' loads
-// are issued before they are added.
+// are issued before they are added (past the last, that one again).
 __device__ __forceinline__ float dv_sum(const float* __restrict__ part, int ks, int B, int N, int b,
                                         int n) {
   const int64_t stride = (int64_t)B * N;
   const float* p = part + (int64_t)b * N + n;
   float v = 0.f;
-  int s = 0;
-  for (; s + 8 <= ks; s += 8) {
+  for (int s = 0; s < ks; s += 8) {
     float t[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = p[(s + u) * stride];
+    for (int u = 0; u < 8; ++u) t[u] = p[min(s + u, ks - 1) * stride];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v += t[u];
+    for (int u = 0; u < 8; ++u)
+      if (s + u < ks) v += t[u];
   }
-  for (; s < ks; ++s) v += p[s * stride];
   return v;
 }
+
+// The bf16 product on the matrix cores: part[ky][b][n] for 128 columns, 16
+// sequences and NW 32-deep K steps per workgroup, one step a wave.  A lane
+// loads eight rows of one 16-byte column vector (16 lanes cover the 128
+// columns, the four lane groups 32 rows), all in flight together, and turns
+// the 8 x 8 block so that register set c holds column c's eight k values:
+// the first operand of a matrix instruction whose row i is column 8 i + c.
+// The second operand is x itself, one 16-byte load a lane.  Eight
+// instructions then leave lane (b, lg) with 32 consecutive columns of
+// sequence b.  Against multiply-adds with the sums handed around by 56
+// shuffles a lane (the float32 kernel above) the launch went from 5.8 to
+// 3.7 us at B = 8, D = 768; it is bound by its loads' latency (two waves a
+// workgroup, and twice the splits, were slower for the kernels that add them).
+//
+// FINISH: x is not read but formed, h = the sum of the splits of o Wo in
+// split order, as wo_finish would: every workgroup adds up its own rows'
+// splits, and those of the first column tile also append h to the block
+// cache (slot off) and write its pooling-score parts.  5.3 us, where the
+// finishing kernel and the product took 3.1 and 5.8.
+struct DvFinish {
+  const float* part;  // [ks][B][K]
+  int ks;
+  const bf16* wp;
+  bf16* Hc;
+  float* spc;
+  int L, off;
+};
+
+template <int NW, bool FINISH>
+__global__ __launch_bounds__(NW * 64) void dec_mfma_part_kernel(const bf16* __restrict__ x,
+                                                                int64_t ldx, int B, DvW<bf16> w,
+                                                                int K, int N,
+                                                                float* __restrict__ part,
+                                                                DvFinish f) {
+  constexpr int CT = 128, LD = CT + 4;
+  __shared__ __attribute__((aligned(16))) float red[NW][16][LD];
+  __shared__ float sred[NW][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lr = lane & 15, lg = lane >> 4;
+  const int n0 = blockIdx.x * CT, b0 = blockIdx.z * 16;
+  const int k = (blockIdx.y * NW + wave) * 32 + lg * 8;  // K is a multiple of 32
+  const int col = n0 + lr * 8, b = b0 + lr;
+  const bool kin = k < K;
+  bf16x8 wv[8];
+  if (kin && col < N) {
+    const bf16* p = w.col(col) + (int64_t)k * w.ld;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) wv[j] = load16(p + (int64_t)j * w.ld);
+  } else {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) wv[j] = bf16x8{};
+  }
+  bf16x8 xf = {};
+  if constexpr (FINISH) {
+    float h[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    float sc = 0.f;
+    if (kin && b < B) {
+      const float* p = f.part + (int64_t)b * K + k;
+      const int64_t stride = (int64_t)B * K;
+      for (int s0 = 0; s0 < f.ks; s0 += 8) {
+        float t[8][8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) ld8(p + (int64_t)min(s0 + u, f.ks - 1) * stride, t[u]);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (s0 + u < f.ks) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) h[e] += t[u][e];
+          }
+      }
+#pragma unroll
+      for (int e = 0; e < 8; ++e) xf[e] = (bf16)h[e];
+      if (blockIdx.x == 0) {
+        store16(f.Hc + ((int64_t)b * f.L + f.off) * K + k, xf);
+        float wp[8];
+        ld8(f.wp + k, wp);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sc += h[e] * wp[e];
+      }
+    }
+    if (blockIdx.x == 0) {  // 32 columns a wave, two waves a score part
+      sc += __shfl_xor(sc, 16);
+      sc += __shfl_xor(sc, 32);
+      if (lg == 0) sred[wave][lr] = sc;
+    }
+  } else {
+    if (kin && b < B) xf = load16(x + (int64_t)b * ldx + k);
+  }
+  f32x4 acc[8];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    const bf16x8 a = {wv[0][c], wv[1][c], wv[2][c], wv[3][c],
+                      wv[4][c], wv[5][c], wv[6][c], wv[7][c]};
+    acc[c] = mma16(a, xf, f32x4{0.f, 0.f, 0.f, 0.f});
+  }
+  // acc[c][r]: column (4 lg + r) 8 + c of sequence lr
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    float* q = &red[wave][lr][lg * 32 + r * 8];
+    store4(q, acc[0][r], acc[1][r], acc[2][r], acc[3][r]);
+    store4(q + 4, acc[4][r], acc[5][r], acc[6][r], acc[7][r]);
+  }
+  __syncthreads();
+  const int nb = min(16, B - b0), nc = min(CT, N - n0);
+  for (int e = tid; e < nb * (CT / 4); e += NW * 64) {
+    const int bb = e / (CT / 4), c = e % (CT / 4) * 4;
+    if (c >= nc) continue;
+    f32x4 t = *reinterpret_cast<const f32x4*>(&red[0][bb][c]);
+#pragma unroll
+    for (int v = 1; v < NW; ++v) t += *reinterpret_cast<const f32x4*>(&red[v][bb][c]);
+    *reinterpret_cast<f32x4*>(part + ((int64_t)blockIdx.y * B + b0 + bb) * N + n0 + c) = t;
+  }
+  if constexpr (FINISH) {
+    const int pair = tid >> 4, bb = tid & 15;  // NW / 2 parts of 64 columns, 16 sequences
+    const int at = blockIdx.y * (NW / 2) + pair;
+    if (blockIdx.x == 0 && pair < NW / 2 && at < K / 64 && b0 + bb < B)
+      f.spc[((int64_t)(b0 + bb) * f.L + f.off) * (K / 64) + at] =
+          sred[2 * pair][bb] + sred[2 * pair + 1][bb];
+  }
+}
+
+// Waves (32-deep K steps) of a workgroup of the kernel above.
+constexpr int kDvWaves = 4;
 
 // h = o Wo into the block cache at slot off, and per 64 columns the part of
 // the pooling score h . wp.  Thread = column n of sequence blockIdx.y.
@@ -430,8 +555,12 @@ int dec_max_batch() { return kDecMaxBatch; }
 int dec_score_parts(int D) { return D / 64; }
 
 int dec_splits(DType dt, int K, int N, int B) {
+  if (dt == DType::BF16) {
+    const int kc = 32 * kDvWaves;
+    return (K + kc - 1) / kc;
+  }
   int kc;
-  return dv_plan(K, N, B, dt == DType::BF16 ? dv_cols<bf16>() : dv_cols<float>(), &kc);
+  return dv_plan(K, N, B, dv_cols<float>(), &kc);
 }
 
 size_t dec_part_bytes(DType dt, int B, int D) {
@@ -442,14 +571,14 @@ size_t dec_part_bytes(DType dt, int B, int D) {
 
 hipError_t dec_product(DType dt, const void* x, int64_t ldx, const void* W0, const void* W1,
                        const void* W2, int B, int D, int N, float* part, hipStream_t s) {
-  int kc;
   if (dt == DType::BF16) {
-    const int ks = dv_plan(D, N, B, dv_cols<bf16>(), &kc);
     const DvW<bf16> w{{(const bf16*)W0, (const bf16*)(W1 ? W1 : W0), (const bf16*)(W2 ? W2 : W0)},
                       D, D};
-    hipLaunchKernelGGL(dec_gemv_part_kernel<bf16>, dim3(N / dv_cols<bf16>(), ks, (B + kDvB - 1) / kDvB),
-                       dim3(256), 0, s, (const bf16*)x, ldx, B, w, D, N, kc, part);
+    const dim3 grid((N + 127) / 128, dec_splits(dt, D, N, B), (B + 15) / 16);
+    hipLaunchKernelGGL((dec_mfma_part_kernel<kDvWaves, false>), grid, dim3(64 * kDvWaves), 0, s,
+                       (const bf16*)x, ldx, B, w, D, N, part, DvFinish{});
   } else {
+    int kc;
     const int ks = dv_plan(D, N, B, dv_cols<float>(), &kc);
     const DvW<float> w{
         {(const float*)W0, (const float*)(W1 ? W1 : W0), (const float*)(W2 ? W2 : W0)}, D, D};
@@ -457,6 +586,17 @@ hipError_t dec_product(DType dt, const void* x, int64_t ldx, const void* W0, con
                        dim3(N / dv_cols<float>(), ks, (B + kDvB - 1) / kDvB), dim3(256), 0, s,
                        (const float*)x, ldx, B, w, D, N, kc, part);
   }
+  return hipGetLastError();
+}
+
+hipError_t dec_finish_product(const float* wo_part, int ks, const void* wp, void* Hc, float* spc,
+                              const void* W, int B, int D, int L, int off, float* part,
+                              hipStream_t s) {
+  const DvW<bf16> w{{(const bf16*)W, (const bf16*)W, (const bf16*)W}, D, D};
+  hipLaunchKernelGGL((dec_mfma_part_kernel<kDvWaves, true>),
+                     dim3((D + 127) / 128, dec_splits(DType::BF16, D, D, B), (B + 15) / 16),
+                     dim3(64 * kDvWaves), 0, s, nullptr, 0, B, w, D, D, part,
+                     DvFinish{wo_part, ks, (const bf16*)wp, (bf16*)Hc, spc, L, off});
   return hipGetLastError();
 }
 
@@ -471,15 +611,10 @@ hipError_t dec_attn(DType dt, const float* part, int ks, void* Kc, void* Vc, voi
   return hipGetLastError();
 }
 
-hipError_t dec_wo_finish(DType dt, const float* part, int ks, const void* wp, void* Hc, float* spc,
-                         int B, int D, int L, int off, hipStream_t s) {
-  const dim3 grid((D + 255) / 256, B);
-  if (dt == DType::BF16)
-    hipLaunchKernelGGL(dec_wo_finish_kernel<bf16>, grid, dim3(256), 0, s, part, ks, B, D,
-                       (const bf16*)wp, (bf16*)Hc, spc, L, off);
-  else
-    hipLaunchKernelGGL(dec_wo_finish_kernel<float>, grid, dim3(256), 0, s, part, ks, B, D,
-                       (const float*)wp, (float*)Hc, spc, L, off);
+hipError_t dec_wo_finish(const float* part, int ks, const void* wp, void* Hc, float* spc, int B,
+                         int D, int L, int off, hipStream_t s) {
+  hipLaunchKernelGGL(dec_wo_finish_kernel<float>, dim3((D + 255) / 256, B), dim3(256), 0, s, part,
+                     ks, B, D, (const float*)wp, (float*)Hc, spc, L, off);
   return hipGetLastError();
 }
 

@@ -311,9 +311,13 @@ hipError_t dec_product(DType dt, const void* x, int64_t ldx, const void* W0, con
 // Adds the QKV splits (k and v to the caches at off), then attention -> o.
 hipError_t dec_attn(DType dt, const float* part, int ks, void* Kc, void* Vc, void* o, int B, int D,
                     int H, int L, int off, hipStream_t s);
-// h = sum of the splits -> Hc at off, with its score parts -> spc.
-hipError_t dec_wo_finish(DType dt, const float* part, int ks, const void* wp, void* Hc, float* spc,
-                         int B, int D, int L, int off, hipStream_t s);
+// h = sum of the splits -> Hc at off, with its score parts -> spc (float32).
+hipError_t dec_wo_finish(const float* part, int ks, const void* wp, void* Hc, float* spc, int B,
+                         int D, int L, int off, hipStream_t s);
+// In bf16 that and the next product h W -> part (not wo_part) in one launch.
+hipError_t dec_finish_product(const float* wo_part, int ks, const void* wp, void* Hc, float* spc,
+                              const void* W, int B, int D, int L, int off, float* part,
+                              hipStream_t s);
 // y = h + sigmoid(u) C (+ x), u = sum of the splits.
 hipError_t dec_gate_finish(DType dt, const float* part, int ks, const void* Hc, const float* C,
                            const void* x, void* y, int B, int D, int L, int off, hipStream_t s);

@@ -489,16 +489,17 @@ template <int NW>
 __global__ __launch_bounds__(NW * 64, 3) void attn_fwd_bf16_kernel(const bf16* __restrict__ qkv,
                                                                bf16* __restrict__ out,
                                                                float* __restrict__ lse, int Tn,
-                                                               int D, int H, int L, float sl2) {
+                                                               int D, int H, int L, int ntile, float sl2) {
   constexpr int QT = NW * 32;
   constexpr int NI = 16 / NW;  // direct loads per wave per key tile (K and V)
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const int b = blockIdx.z / H, h = blockIdx.z % H;
+  const AttnTile at = attn_tile(ntile, true);
+  const int b = at.bh / H, h = at.bh % H;
   const int bs = blockIdx.y * L;
   const int be = min(bs + L, Tn);
-  const int q0 = bs + blockIdx.x * QT;
+  const int q0 = bs + at.tile * QT;
   if (q0 >= be) return;
   const int64_t rs = 3LL * D;
   const bf16* base = qkv + (int64_t)b * Tn * rs + h * kDh;
@@ -649,16 +650,17 @@ template <int NW>
 __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_bf16_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ o, const bf16* __restrict__ dout,
     const float* __restrict__ lse, float* __restrict__ delta, bf16* __restrict__ dqkv, int Tn,
-    int D, int H, int L, float sl2, float scale) {
+    int D, int H, int L, int ntile, float sl2, float scale) {
   constexpr int QT = NW * 32;
   constexpr int NI = 16 / NW;
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const int b = blockIdx.z / H, h = blockIdx.z % H;
+  const AttnTile at = attn_tile(ntile, true);
+  const int b = at.bh / H, h = at.bh % H;
   const int bs = blockIdx.y * L;
   const int be = min(bs + L, Tn);
-  const int q0 = bs + blockIdx.x * QT;
+  const int q0 = bs + at.tile * QT;
   if (q0 >= be) return;
   const int64_t rs = 3LL * D;
   const bf16* base = qkv + (int64_t)b * Tn * rs + h * kDh;
@@ -780,7 +782,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_bf16_kernel(
 template <int NW>
 __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_bf16_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ dout, const float* __restrict__ lse,
-    const float* __restrict__ delta, bf16* __restrict__ dqkv, int Tn, int D, int H, int L,
+    const float* __restrict__ delta, bf16* __restrict__ dqkv, int Tn, int D, int H, int L, int ntile,
     float sl2, float scale) {
   constexpr int KT = NW * 32;
   constexpr int NI = 16 / NW;
@@ -788,10 +790,11 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_bf16_kernel(
   __shared__ __attribute__((aligned(16))) float vec_s[2][2][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const int b = blockIdx.z / H, h = blockIdx.z % H;
+  const AttnTile at = attn_tile(ntile, false);
+  const int b = at.bh / H, h = at.bh % H;
   const int bs = blockIdx.y * L;
   const int be = min(bs + L, Tn);
-  const int k0 = bs + blockIdx.x * KT;
+  const int k0 = bs + at.tile * KT;
   if (k0 >= be) return;
   const int64_t rs = 3LL * D;
   const bf16* base = qkv + (int64_t)b * Tn * rs + h * kDh;
@@ -1328,9 +1331,10 @@ hipError_t attn_fwd(DType dt, const void* qkv, void* out, float* lse, int B, int
   if (dt == DType::BF16) {
     const int nw = attn_waves(L, T);
     const int lb = L < T ? L : T;
-    dim3 grid((lb + nw * 32 - 1) / (nw * 32), (T + L - 1) / L, B * H);
+    const int nt = (lb + nw * 32 - 1) / (nw * 32);
+    const dim3 grid = attn_grid(nt, (T + L - 1) / L, B * H);
     const float sl2 = 1.4426950408889634f / sqrtf((float)kDh);
-#define FWD(NW) hipLaunchKernelGGL(attn_fwd_bf16_kernel<NW>, grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (bf16*)out, lse, T, D, H, L, sl2)
+#define FWD(NW) hipLaunchKernelGGL(attn_fwd_bf16_kernel<NW>, grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (bf16*)out, lse, T, D, H, L, nt, sl2)
     if (nw == 1) FWD(1); else if (nw == 2) FWD(2); else FWD(4);
 #undef FWD
     return hipGetLastError();
@@ -1346,10 +1350,11 @@ hipError_t attn_bwd_dq(DType dt, const void* qkv, const void* out, const void* d
   if (dt == DType::BF16) {
     const int nw = attn_waves(L, T);
     const int lb = L < T ? L : T;
-    dim3 grid((lb + nw * 32 - 1) / (nw * 32), (T + L - 1) / L, B * H);
+    const int nt = (lb + nw * 32 - 1) / (nw * 32);
+    const dim3 grid = attn_grid(nt, (T + L - 1) / L, B * H);
     const float scale = 1.0f / sqrtf((float)kDh);
     const float sl2 = 1.4426950408889634f * scale;
-#define DQ(NW) hipLaunchKernelGGL(attn_bwd_dq_bf16_kernel<NW>, grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (const bf16*)out, (const bf16*)dout, lse, delta, (bf16*)dqkv, T, D, H, L, sl2, scale)
+#define DQ(NW) hipLaunchKernelGGL(attn_bwd_dq_bf16_kernel<NW>, grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (const bf16*)out, (const bf16*)dout, lse, delta, (bf16*)dqkv, T, D, H, L, nt, sl2, scale)
     if (nw == 1) DQ(1); else if (nw == 2) DQ(2); else DQ(4);
 #undef DQ
     return hipGetLastError();
@@ -1386,10 +1391,11 @@ hipError_t attn_bwd_dkdv(DType dt, const void* qkv, const void* dout, const floa
   if (dt == DType::BF16) {
     const int nw = attn_waves(L, T);
     const int lb = L < T ? L : T;
-    dim3 grid((lb + nw * 32 - 1) / (nw * 32), (T + L - 1) / L, B * H);
+    const int nt = (lb + nw * 32 - 1) / (nw * 32);
+    const dim3 grid = attn_grid(nt, (T + L - 1) / L, B * H);
     const float scale = 1.0f / sqrtf((float)kDh);
     const float sl2 = 1.4426950408889634f * scale;
-#define DKDV(NW) hipLaunchKernelGGL(attn_bwd_dkdv_bf16_kernel<NW>, grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (const bf16*)dout, lse, (const float*)delta, (bf16*)dqkv, T, D, H, L, sl2, scale)
+#define DKDV(NW) hipLaunchKernelGGL(attn_bwd_dkdv_bf16_kernel<NW>, grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (const bf16*)dout, lse, (const float*)delta, (bf16*)dqkv, T, D, H, L, nt, sl2, scale)
     if (nw == 1) DKDV(1); else if (nw == 2) DKDV(2); else DKDV(4);
 #undef DKDV
     return hipGetLastError();

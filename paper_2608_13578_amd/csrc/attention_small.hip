@@ -315,17 +315,18 @@ __device__ __forceinline__ void sm_vm_wait() {
 template <int NW, int DH>
 __global__ __launch_bounds__(NW * 64) void attn_small_fwd_mfma_kernel(
     const bf16* __restrict__ qkv, bf16* __restrict__ out, float* __restrict__ lse, int Tn, int D,
-    int H, int L, float sl2) {
+    int H, int L, int ntile, float sl2) {
   constexpr int QT = NW * 32;
   constexpr int NI = 2 * (DH / 8) / NW;  // direct loads per wave per K / V tile pair
   constexpr int NJ = DH / 16;            // 16-wide column tiles of the output
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * DH];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const int b = blockIdx.z / H, h = blockIdx.z % H;
+  const AttnTile at = attn_tile(ntile, true);
+  const int b = at.bh / H, h = at.bh % H;
   const int bs = blockIdx.y * L;
   const int be = min(bs + L, Tn);
-  const int q0 = bs + blockIdx.x * QT;
+  const int q0 = bs + at.tile * QT;
   if (q0 >= be) return;
   const int64_t rs = 3LL * D;
   const bf16* base = qkv + (int64_t)b * Tn * rs + h * DH;
@@ -465,17 +466,18 @@ template <int NW, int DH>
 __global__ __launch_bounds__(NW * 64) void attn_small_dq_mfma_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ o, const bf16* __restrict__ dout,
     const float* __restrict__ lse, float* __restrict__ delta, bf16* __restrict__ dqkv, int Tn,
-    int D, int H, int L, float sl2, float scale) {
+    int D, int H, int L, int ntile, float sl2, float scale) {
   constexpr int QT = NW * 32;
   constexpr int NI = 2 * (DH / 8) / NW;
   constexpr int NJ = DH / 16;
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * DH];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const int b = blockIdx.z / H, h = blockIdx.z % H;
+  const AttnTile at = attn_tile(ntile, true);
+  const int b = at.bh / H, h = at.bh % H;
   const int bs = blockIdx.y * L;
   const int be = min(bs + L, Tn);
-  const int q0 = bs + blockIdx.x * QT;
+  const int q0 = bs + at.tile * QT;
   if (q0 >= be) return;
   const int64_t rs = 3LL * D;
   const bf16* base = qkv + (int64_t)b * Tn * rs + h * DH;
@@ -589,7 +591,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_dq_mfma_kernel(
 template <int NW, int DH>
 __global__ __launch_bounds__(NW * 64) void attn_small_dkdv_mfma_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ dout, const float* __restrict__ lse,
-    const float* __restrict__ delta, bf16* __restrict__ dqkv, int Tn, int D, int H, int L,
+    const float* __restrict__ delta, bf16* __restrict__ dqkv, int Tn, int D, int H, int L, int ntile,
     float sl2, float scale) {
   constexpr int KT = NW * 32;
   constexpr int NI = 2 * (DH / 8) / NW;
@@ -598,10 +600,11 @@ __global__ __launch_bounds__(NW * 64) void attn_small_dkdv_mfma_kernel(
   __shared__ __attribute__((aligned(16))) float vec_s[2][2][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const int b = blockIdx.z / H, h = blockIdx.z % H;
+  const AttnTile at = attn_tile(ntile, false);
+  const int b = at.bh / H, h = at.bh % H;
   const int bs = blockIdx.y * L;
   const int be = min(bs + L, Tn);
-  const int k0 = bs + blockIdx.x * KT;
+  const int k0 = bs + at.tile * KT;
   if (k0 >= be) return;
   const int64_t rs = 3LL * D;
   const bf16* base = qkv + (int64_t)b * Tn * rs + h * DH;
@@ -732,17 +735,18 @@ hipError_t small_bwd_mfma(int pass, const void* qkv, const void* o, const void* 
                           int L, hipStream_t s) {
   const int lb = L < Tn ? L : Tn;
   const int nw = small_waves(lb);
-  const dim3 grid((lb + nw * 32 - 1) / (nw * 32), (Tn + L - 1) / L, B * H);
+  const int nt = (lb + nw * 32 - 1) / (nw * 32);
+  const dim3 grid = attn_grid(nt, (Tn + L - 1) / L, B * H);
   const float scale = 1.0f / sqrtf((float)DH);
   const float sl2 = 1.4426950408889634f * scale;
 #define SDQ(NW)                                                                               \
   hipLaunchKernelGGL((attn_small_dq_mfma_kernel<NW, DH>), grid, dim3(NW * 64), 0, s,           \
                      (const bf16*)qkv, (const bf16*)o, (const bf16*)dout, lse, delta,           \
-                     (bf16*)dqkv, Tn, D, H, L, sl2, scale)
+                     (bf16*)dqkv, Tn, D, H, L, nt, sl2, scale)
 #define SDKDV(NW)                                                                             \
   hipLaunchKernelGGL((attn_small_dkdv_mfma_kernel<NW, DH>), grid, dim3(NW * 64), 0, s,         \
                      (const bf16*)qkv, (const bf16*)dout, lse, (const float*)delta,             \
-                     (bf16*)dqkv, Tn, D, H, L, sl2, scale)
+                     (bf16*)dqkv, Tn, D, H, L, nt, sl2, scale)
   if (pass == 1) {
     if (nw == 1) SDQ(1);
     else if (nw == 2) SDQ(2);
@@ -762,11 +766,12 @@ hipError_t small_fwd_mfma(const void* qkv, void* out, float* lse, int B, int Tn,
                           int L, hipStream_t s) {
   const int lb = L < Tn ? L : Tn;
   const int nw = small_waves(lb);
-  const dim3 grid((lb + nw * 32 - 1) / (nw * 32), (Tn + L - 1) / L, B * H);
+  const int nt = (lb + nw * 32 - 1) / (nw * 32);
+  const dim3 grid = attn_grid(nt, (Tn + L - 1) / L, B * H);
   const float sl2 = 1.4426950408889634f / sqrtf((float)DH);
 #define SFWD(NW)                                                                              \
   hipLaunchKernelGGL((attn_small_fwd_mfma_kernel<NW, DH>), grid, dim3(NW * 64), 0, s,          \
-                     (const bf16*)qkv, (bf16*)out, lse, Tn, D, H, L, sl2)
+                     (const bf16*)qkv, (bf16*)out, lse, Tn, D, H, L, nt, sl2)
   if (nw == 1) SFWD(1);
   else if (nw == 2) SFWD(2);
   else SFWD(4);

@@ -603,8 +603,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
   // part; the launcher checks that the part length is a multiple of BK).
   auto bslab = [&](int k) {
     if constexpr (BSEG == kSegK) {
-      const int sg = k / B.seg_len;
-      return lb.slab(B.p[sg], B.ld, k - sg * B.seg_len);
+      const int sl = B.seg_len;
+      const bf16* p = k < sl ? B.p[0] : k < 2 * sl ? B.p[1] : B.p[2];
+      return lb.slab(p, B.ld, k < sl ? k : k < 2 * sl ? k - sl : k - 2 * sl);
     } else {
       return lb.slab(bptr, B.ld, k);
     }

@@ -463,9 +463,11 @@ struct PipeLoad {
     }
   }
   // Bytes the slab at k may touch: of a last, partial slab only the k-rows
-  // below kend (row-contiguous; the others then read as zero).
+  // below kend (row-contiguous; the others then read as zero).  Only a
+  // product of two row-contiguous operands may have one (TAIL).
+  template <bool TAIL>
   __device__ __forceinline__ uint32_t extent_at(int k, int kend) const {
-    if constexpr (!RCONTIG) return extent;
+    if constexpr (!(RCONTIG && TAIL)) return extent;
     else return extent - (uint32_t)max(0, k + BK - kend) * pitch;
   }
 
@@ -581,6 +583,7 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
   Epi epi = epi0;
   bind_split(epi, z);
   const int kend = min(K, kbeg + kchunk);
+  constexpr bool TAIL = A_MC && B_NC;
   const int nk = kend > kbeg ? (kend - kbeg + BK - 1) / BK : 0;
 
   // B split along N: every part has column tiles of its own (the last one
@@ -668,8 +671,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
     if (st < nk) {
       bf16* sa = lds + st * STAGE;
       const int k = kbeg + st * BK;
-      la.issue(la.slab(A.p[0], A.ld, k), la.extent_at(k, kend), sa, wave);
-      lb.issue(bslab(k), lb.extent_at(k, kend), sa + AEL, wave);
+      la.issue(la.slab(A.p[0], A.ld, k), la.template extent_at<TAIL>(k, kend), sa, wave);
+      lb.issue(bslab(k), lb.template extent_at<TAIL>(k, kend), sa + AEL, wave);
     }
   }
   if (nk > 0) {
@@ -700,8 +703,8 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
             if (nxt < nk) {
               bf16* sn = buf(kt);
               const int k = kbeg + nxt * BK;
-              la.issue(la.slab(A.p[0], A.ld, k), la.extent_at(k, kend), sn, wave);
-              lb.issue(bslab(k), lb.extent_at(k, kend), sn + AEL, wave);
+              la.issue(la.slab(A.p[0], A.ld, k), la.template extent_at<TAIL>(k, kend), sn, wave);
+              lb.issue(bslab(k), lb.template extent_at<TAIL>(k, kend), sn + AEL, wave);
             }
             read_step(buf(kt + 1), 0, fa[c ^ 1], fb[c ^ 1]);
           }
@@ -805,6 +808,7 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(int M, int N, int K,
   Epi epi = epi0;
   bind_split(epi, z);
   const int kend = min(K, kbeg + kchunk);
+  constexpr bool TAIL = A_MC && B_NC;
   const int nk = (kend - kbeg + BK - 1) / BK;  // at least 1
 
   const bf16* bptr = B.p[0];
@@ -872,8 +876,8 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(int M, int N, int K,
     const bool load = kt + 2 < nk;
     const int k = kbeg + (load ? kt + 2 : kt) * BK;
     const __amdgpu_buffer_rsrc_t rsa =
-        la.rsrc(la.slab(A.p[0], A.ld, k), load ? la.extent_at(k, kend) : 0);
-    const __amdgpu_buffer_rsrc_t rsb = lb.rsrc(bslab(k), load ? lb.extent_at(k, kend) : 0);
+        la.rsrc(la.slab(A.p[0], A.ld, k), load ? la.template extent_at<TAIL>(k, kend) : 0);
+    const __amdgpu_buffer_rsrc_t rsb = lb.rsrc(bslab(k), load ? lb.template extent_at<TAIL>(k, kend) : 0);
     bf16* sa = lds + (kt & 1) * kStage;
     asm volatile("s_nop 2");
     unrolled<64>([&](auto ix) {
@@ -914,8 +918,8 @@ __global__ __launch_bounds__(256, 1) void gemm_wide_kernel(int M, int N, int K,
 #pragma unroll
   for (int st = 0; st < 2; ++st) {
     const int k = kbeg + min(st, nk - 1) * BK;
-    la.issue(la.slab(A.p[0], A.ld, k), la.extent_at(k, kend), lds + st * kStage, wave);
-    lb.issue(bslab(k), lb.extent_at(k, kend), lds + (2 + st) * kStage, wave);
+    la.issue(la.slab(A.p[0], A.ld, k), la.template extent_at<TAIL>(k, kend), lds + st * kStage, wave);
+    lb.issue(bslab(k), lb.template extent_at<TAIL>(k, kend), lds + (2 + st) * kStage, wave);
   }
   wait_vmcnt<NLD>();
   __builtin_amdgcn_s_barrier();
@@ -1472,7 +1476,8 @@ hipError_t launch_pipe(const GemmDesc& g, const Epi& epi, hipStream_t s) {
   {
     const int sp = g.splits < 1 ? 1 : g.splits;
     const int kc = g.kchunk > 0 ? g.kchunk : ((g.K + sp - 1) / sp + 63) / 64 * 64;
-    if (wide_ok(g, kc, (g.K + kc - 1) / kc, epi_cost((const Epi*)nullptr))) return launch_wide<AMC, BNC, SEG>(g, epi, s);
+    if (wide_ok(g, kc, (g.K + kc - 1) / kc, epi_cost((const Epi*)nullptr)))
+      return launch_wide<AMC, BNC, SEG>(g, epi, s);
   }
   if constexpr (AMC) {
     int splits = g.splits < 1 ? 1 : g.splits;

@@ -497,7 +497,7 @@ __global__ __launch_bounds__(NW * 64, 3) void attn_fwd_bf16_kernel(const bf16* _
   const int lr = lane & 15, lg = lane >> 4;
   const AttnTile at = attn_tile(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
-  const int bs = blockIdx.y * L;
+  const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
   const int q0 = bs + at.tile * QT;
   if (q0 >= be) return;
@@ -658,7 +658,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_bf16_kernel(
   const int lr = lane & 15, lg = lane >> 4;
   const AttnTile at = attn_tile(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
-  const int bs = blockIdx.y * L;
+  const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
   const int q0 = bs + at.tile * QT;
   if (q0 >= be) return;
@@ -792,7 +792,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_bf16_kernel(
   const int lr = lane & 15, lg = lane >> 4;
   const AttnTile at = attn_tile(ntile, false);
   const int b = at.bh / H, h = at.bh % H;
-  const int bs = blockIdx.y * L;
+  const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
   const int k0 = bs + at.tile * KT;
   if (k0 >= be) return;

@@ -324,7 +324,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_fwd_mfma_kernel(
   const int lr = lane & 15, lg = lane >> 4;
   const AttnTile at = attn_tile(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
-  const int bs = blockIdx.y * L;
+  const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
   const int q0 = bs + at.tile * QT;
   if (q0 >= be) return;
@@ -475,7 +475,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_dq_mfma_kernel(
   const int lr = lane & 15, lg = lane >> 4;
   const AttnTile at = attn_tile(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
-  const int bs = blockIdx.y * L;
+  const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
   const int q0 = bs + at.tile * QT;
   if (q0 >= be) return;
@@ -602,7 +602,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_dkdv_mfma_kernel(
   const int lr = lane & 15, lg = lane >> 4;
   const AttnTile at = attn_tile(ntile, false);
   const int b = at.bh / H, h = at.bh % H;
-  const int bs = blockIdx.y * L;
+  const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
   const int k0 = bs + at.tile * KT;
   if (k0 >= be) return;

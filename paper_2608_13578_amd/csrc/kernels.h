@@ -164,25 +164,40 @@ hipError_t attn_small_dkdv(DType dt, const void* qkv, const void* dout, const fl
                            hipStream_t s);
 
 // The workgroup of a blocked attention kernel: query (or key) tile `tile` of
-// block blockIdx.y, sequence x head bh.  Where a block has several tiles
-// (ntile > 1) their causal work differs, so the longest start first: the
-// tile is the slowest index, from the last one down where later tiles see
+// block `blk`, sequence x head bh.  Where a block has several tiles
+// (ntile > 1) their causal work differs, so the longest start first, of a
+// group of blocks at a time: from the last tile down where later tiles see
 // more keys (`last_first`) and from the first one up where earlier keys are
-// seen by more queries.  Sequence x head is then the fastest index, and
-// mostly a multiple of the 8 XCDs, so that a head's tiles share an L2.
-// At B = 8, T = L = 1024, 12 heads of 64 the forward, dQ and dK / dV took 54,
-// 95 and 135 us with the tiles of a block next to each other in first-to-last
-// order, and take 36, 58 and 85 us in this one.
+// seen by more queries.  Sequence x head is the fastest index, and mostly a
+// multiple of the 8 XCDs, so that a head's tiles share an L2.  Grid:
+// (sequence x head, tile and block of the group, group); the last group may
+// hold blocks past the sequence, whose workgroups find no rows and return.
+//
+// Three tiles and more: one group.  At B = 8, T = L = 1024, 12 heads of 64 the
+// forward, dQ and dK / dV took 54, 95 and 135 us with the tiles of a block
+// next to each other in first-to-last order, and take 36, 58 and 85 us; at
+// B = 2, T = 16384, L = 1024 183, 342 and 525 -> 114, 232 and 338 (in groups
+// of 512 workgroups 127, 237, 357).  Two tiles differ less, and a tile waits
+// so long for the other over a long sequence that the keys have left L2:
+// B = 2, T = 65536, L = 256, 16 heads forward 305 us in the old order, 346 in
+// one group, 321 in groups of 1024 workgroups, 306 of 512 and of 256; B = 1,
+// T = 8192, L = 300 26 -> 21 us in one group and in groups of 512.
 struct AttnTile {
-  int tile, bh;
+  int tile, blk, bh;
 };
 inline __device__ AttnTile attn_tile(int ntile, bool last_first) {
-  if (ntile == 1) return {0, (int)blockIdx.z};
-  const int t = (int)blockIdx.z;
-  return {last_first ? ntile - 1 - t : t, (int)blockIdx.x};
+  if (ntile == 1) return {0, (int)blockIdx.y, (int)blockIdx.z};
+  const int g = (int)gridDim.y / ntile, t = (int)blockIdx.y / g;
+  return {last_first ? ntile - 1 - t : t, (int)(blockIdx.z * g + blockIdx.y % g),
+          (int)blockIdx.x};
 }
 inline dim3 attn_grid(int ntile, int nblk, int bh) {
-  return ntile == 1 ? dim3(1, nblk, bh) : dim3(bh, nblk, ntile);
+  if (ntile == 1) return dim3(1, nblk, bh);
+  // 32768: the limit of the grid's second dimension is 65535
+  const int64_t most = ntile == 2 ? 512 / (2 * (int64_t)bh) : 32768 / ntile;
+  const int cap = most < 1 ? 1 : most > nblk ? nblk : (int)most;
+  const int groups = (nblk + cap - 1) / cap, g = (nblk + groups - 1) / groups;
+  return dim3(bh, g * ntile, groups);
 }
 
 // ------------------------------------------------------------------ memory path

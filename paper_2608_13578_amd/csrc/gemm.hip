@@ -106,8 +106,22 @@ struct HasPre<Epi, std::void_t<typename Epi::Pre>> {
   static constexpr bool value = true;
 };
 
+// What the choice of a kernel needs to know of an epilogue.
+enum EpiKind {
+  kEpiStore = 0,
+  kEpiScore = 1,
+  kEpiGate = 2,
+  kEpiHbar = 3,
+  kEpiGelu = 4,
+  kEpiGeluBwd = 5,
+  kEpiHeadStats = 6,
+  kEpiHeadGrad = 7,
+  kEpiPartial = 8,
+};
+
 template <typename TO, typename TA>
 struct EpiStore {
+  static constexpr EpiKind kKind = kEpiStore;
   TO* C;
   int64_t ldc;
   const TA* add;
@@ -153,6 +167,7 @@ __device__ __forceinline__ float gelu_grad_f(float u) {
 // and A = gelu(U) of the rounded U.
 template <typename T>
 struct EpiGelu {
+  static constexpr EpiKind kKind = kEpiGelu;
   T* U;
   T* A;
   int64_t ld;
@@ -173,6 +188,7 @@ struct EpiGelu {
 // Backward through the GELU: dU = acc * gelu'(U), U the stored forward value.
 template <typename T>
 struct EpiGeluBwd {
+  static constexpr EpiKind kKind = kEpiGeluBwd;
   const T* U;
   T* dU;
   int64_t ld;
@@ -203,6 +219,7 @@ struct EpiGeluBwd {
 // sp[m * (N / 64) + n0 / 64]; the pooling kernel adds the N / 64 parts.
 template <typename T>
 struct EpiScore {
+  static constexpr EpiKind kKind = kEpiScore;
   T* C;
   int64_t ldc;
   const T* wp;
@@ -231,6 +248,7 @@ struct EpiScore {
 // Split-K partial tile: split z of an M x N product goes to P + z * M * N
 // (the kernel moves P to its split's slice through bind_split).
 struct EpiPartial {
+  static constexpr EpiKind kKind = kEpiPartial;
   float* P;
   int64_t ld;
   int64_t split_stride;
@@ -286,6 +304,7 @@ __global__ __launch_bounds__(256) void wgrad_reduce_kernel(const float* __restri
 
 template <typename T>
 struct EpiGate {
+  static constexpr EpiKind kKind = kEpiGate;
   GateEpi e;
   struct Pre {
     Raw8<T> h, x;
@@ -329,6 +348,7 @@ struct EpiGate {
 
 template <typename T>
 struct EpiHbar {
+  static constexpr EpiKind kKind = kEpiHbar;
   HbarEpi e;
   struct Pre {
     Raw8<T> dy, w;
@@ -525,9 +545,11 @@ struct PipeLoad {
   }
 };
 
-// Tile order.  Workgroups are dealt to the chip's 8 XCDs round-robin in
-// launch order (x fastest, then y, then the split index z), and each XCD has
-// its own L2.  The launch-order index is mapped so that every XCD works
+// Tile order.  The grid is (tile rows, tile columns, splits): rows in x, whose
+// limit of 2^31 - 1 holds any B T, where y and z end at 65535 (64-row tiles
+// would pass that from B T = 4194241 on).  Workgroups are dealt to the chip's 8
+// XCDs round-robin in launch order (x fastest, then y, then the split index z),
+// and each XCD has its own L2.  The launch-order index is mapped so that every XCD works
 // through one contiguous run of the (split, tile) sequence; within a split
 // the sequence walks groups of `group` tile rows column by column.  The
 // launcher picks the group height that keeps the A row panels plus B column
@@ -536,10 +558,10 @@ struct PipeLoad {
 constexpr int kXcds = 8;
 
 __device__ __forceinline__ void xcd_tile_order(int group, int& tm, int& tn, int& z) {
-  const int nx = gridDim.x, ny = gridDim.y;
+  const int nx = gridDim.y, ny = gridDim.x;  // tile columns, tile rows
   const int ntiles = nx * ny;
   const int total = ntiles * gridDim.z;
-  const int bid = (blockIdx.z * ny + blockIdx.y) * nx + blockIdx.x;
+  const int bid = (blockIdx.z * nx + blockIdx.y) * ny + blockIdx.x;
   const int xcd = bid % kXcds, pos = bid / kXcds;
   const int q = total / kXcds, r = total % kXcds;
   int t = xcd < r ? xcd * (q + 1) + pos : r * (q + 1) + (xcd - r) * q + pos;
@@ -1223,6 +1245,7 @@ __device__ __forceinline__ float row16_sum(float v) {
   return v + dpp_mov<0x140>(v);
 }
 struct EpiHeadStats {
+  static constexpr EpiKind kKind = kEpiHeadStats;
   float* part;
   int ntile;
   int V;
@@ -1249,6 +1272,7 @@ struct EpiHeadStats {
   }
 };
 struct EpiHeadGrad {
+  static constexpr EpiKind kKind = kEpiHeadGrad;
   bf16* G;
   int64_t ld;
   const float* lse;
@@ -1345,63 +1369,66 @@ int64_t col_tiles(const GemmDesc& g, int bn) {
   return (g.N + bn - 1) / bn;
 }
 
-// float32 launch: 64 x 64 tiles, or 32 x 64 where those would not give every
-// CU a workgroup (a small layer's B T = 256, D = 128 then has 16 to 48
-// workgroups instead of 2 to 6).  A product whose K may end inside a slab has
-// both operands M/N-contiguous.
+// The kernels, and how a product is dealt to one of them: K in `splits`
+// ranges of kchunk, the rows and columns of the result in tiles.
+enum ProductKernel {
+  kF32Rows32 = 0,  // gemm_f32_kernel, 32 x 64
+  kF32Rows64 = 1,  // gemm_f32_kernel, 64 x 64
+  kPipeRows32 = 2, // gemm_pipe_kernel, 32 x 128
+  kPipe8 = 3,      // gemm_pipe_kernel, 128 x 128, eight waves
+  kPipe4 = 4,      // the same with four waves
+  kWide = 5,       // gemm_wide_kernel, 256 x 256
+};
+struct ProductPlan {
+  ProductKernel kernel;
+  int rows, cols;  // tiles
+  int splits, kchunk;
+};
+dim3 plan_grid(const ProductPlan& p) {
+  return dim3((unsigned)p.rows, (unsigned)p.cols, (unsigned)p.splits);
+}
+
+// The K range of a split, a multiple of the slab depth, unless the caller
+// fixed it, and the number of splits.
+void plan_splits(const GemmDesc& g, int bk, ProductPlan* p) {
+  const int splits = g.splits < 1 ? 1 : g.splits;
+  p->kchunk = g.kchunk > 0 ? g.kchunk : ((g.K + splits - 1) / splits + bk - 1) / bk * bk;
+  p->splits = (g.K + p->kchunk - 1) / p->kchunk;
+}
+
+// float32: 64 x 64 tiles, or 32 x 64 where those would not give every CU a
+// workgroup (a small layer's B T = 256, D = 128 then has 16 to 48 workgroups
+// instead of 2 to 6).
+ProductPlan plan_f32(const GemmDesc& g) {
+  ProductPlan p;
+  plan_splits(g, 32, &p);
+  p.cols = (g.N + 63) / 64;
+  const int64_t tiles = (int64_t)p.cols * ((g.M + 63) / 64) * p.splits;
+  p.kernel = tiles < 256 ? kF32Rows32 : kF32Rows64;
+  p.rows = tiles < 256 ? (g.M + 31) / 32 : (g.M + 63) / 64;
+  return p;
+}
+
 template <int BM, int ST, bool AMC, bool BNC, int SEG, class Epi>
-hipError_t launch_f32_tile(const GemmDesc& g, const Epi& epi, int kchunk, int splits,
-                           hipStream_t s) {
+hipError_t launch_f32_tile(const GemmDesc& g, const ProductPlan& p, const Epi& epi, hipStream_t s) {
   Operand<float, AMC, kSegNone> A{{(const float*)g.A, nullptr, nullptr}, g.lda, 0};
   Operand<float, BNC, SEG> B{{(const float*)g.B[0], (const float*)g.B[1], (const float*)g.B[2]},
                              g.ldb, g.seg_len};
-  const dim3 grid((g.N + 63) / 64, (g.M + BM - 1) / BM, splits);
-  const int group = xcd_group_rows((int)grid.x, (int)grid.y, (int)grid.z);
-  hipLaunchKernelGGL((gemm_f32_kernel<BM, 64, ST, AMC, BNC, SEG, Epi>), grid, dim3(256), 0, s, g.M,
-                     g.N, g.K, A, B, kchunk, group, epi);
+  const int group = xcd_group_rows(p.cols, p.rows, p.splits);
+  hipLaunchKernelGGL((gemm_f32_kernel<BM, 64, ST, AMC, BNC, SEG, Epi>), plan_grid(p), dim3(256), 0,
+                     s, g.M, g.N, g.K, A, B, p.kchunk, group, epi);
   return hipGetLastError();
 }
 
+// A product whose K may end inside a slab has both operands M/N-contiguous.
 template <bool AMC, bool BNC, int SEG, class Epi>
 hipError_t launch_f32(const GemmDesc& g, const Epi& epi, hipStream_t s) {
   if (!(AMC && BNC) && g.K % 32 != 0) return hipErrorInvalidValue;
   if ((AMC && g.M < 4) || g.N < 4) return hipErrorInvalidValue;
   if (SEG != kSegNone && g.seg_len % 64 != 0) return hipErrorInvalidValue;
-  int splits = g.splits < 1 ? 1 : g.splits;
-  int kchunk = ((g.K + splits - 1) / splits + 31) / 32 * 32;
-  if (g.kchunk > 0) kchunk = g.kchunk;
-  splits = (g.K + kchunk - 1) / kchunk;
-  const int64_t tiles = (int64_t)((g.N + 63) / 64) * ((g.M + 63) / 64) * splits;
-  if (tiles < 256) return launch_f32_tile<32, 4, AMC, BNC, SEG>(g, epi, kchunk, splits, s);
-  return launch_f32_tile<64, 3, AMC, BNC, SEG>(g, epi, kchunk, splits, s);
-}
-
-// Pipelined bf16 launch: 128 x 128 tiles, two 32 KB slabs in flight, so
-// that two workgroups share a CU (measured faster on these shapes than a
-// deeper ring with one workgroup per CU).  Eight waves of 64 x 32 by
-// default: more waves to cover the load and LDS latencies, at 1.5x the
-// fragment reads per matrix instruction.  Four waves of 64 x 64 stay on
-// the weight gradients whose operands are both read transposed and that
-// fill the chip with splits, and on products whose B is split along K (the
-// input gradient of Q, K, V): there eight waves measured slower.  The
-// layer's forward + backward step took 308 instead of 316 us.  Needs the K
-// range of every split to be a whole number of 64-wide slabs.
-template <int PBM, int ST, int WGM, int WGN, bool AMC, bool BNC, int SEG, class Epi>
-hipError_t launch_pipe_w(const GemmDesc& g, const Epi& epi, hipStream_t s) {
-  constexpr int PBN = 128, PBK = 64;
-  Operand<bf16, AMC, kSegNone> A{{(const bf16*)g.A, nullptr, nullptr}, g.lda, 0};
-  Operand<bf16, BNC, SEG> B{{(const bf16*)g.B[0], (const bf16*)g.B[1], (const bf16*)g.B[2]}, g.ldb,
-                            g.seg_len};
-  int splits = g.splits < 1 ? 1 : g.splits;
-  int kchunk = (g.K + splits - 1) / splits;
-  kchunk = (kchunk + 63) / 64 * 64;
-  if (g.kchunk > 0) kchunk = g.kchunk;
-  splits = (g.K + kchunk - 1) / kchunk;
-  dim3 grid((unsigned)col_tiles(g, PBN), (g.M + PBM - 1) / PBM, splits);
-  const int group = xcd_group_rows((int)grid.x, (int)grid.y, (int)grid.z);
-  hipLaunchKernelGGL((gemm_pipe_kernel<PBM, PBN, PBK, ST, WGM, WGN, AMC, BNC, SEG, Epi>), grid,
-                     dim3(WGM * WGN * 64), 0, s, g.M, g.N, g.K, A, B, kchunk, group, epi);
-  return hipGetLastError();
+  const ProductPlan p = plan_f32(g);
+  if (p.kernel == kF32Rows32) return launch_f32_tile<32, 4, AMC, BNC, SEG>(g, p, epi, s);
+  return launch_f32_tile<64, 3, AMC, BNC, SEG>(g, p, epi, s);
 }
 
 // Time model (ns) of a bf16 product with `slabs` 64-deep slabs per
@@ -1418,14 +1445,14 @@ struct EpiCost {
   int64_t pipe;  // per 512 tiles of 128 x 128
   int64_t wide;  // per 256 tiles of 256 x 256
 };
-template <class Epi>
-constexpr EpiCost epi_cost(const Epi*) { return {0, 0}; }
-template <class T>
-constexpr EpiCost epi_cost(const EpiScore<T>*) { return {1800, 7300}; }
-template <class T>
-constexpr EpiCost epi_cost(const EpiHbar<T>*) { return {2800, 7800}; }
-template <class T>
-constexpr EpiCost epi_cost(const EpiGate<T>*) { return {9900, 22000}; }
+EpiCost epi_cost(EpiKind kind) {
+  switch (kind) {
+    case kEpiScore: return {1800, 7300};
+    case kEpiHbar: return {2800, 7800};
+    case kEpiGate: return {9900, 22000};
+    default: return {0, 0};
+  }
+}
 
 int64_t pipe_time(int64_t M, int64_t cols, int64_t slabs, int64_t splits, int64_t extra) {
   const int64_t tiles = ((M + 127) / 128) * cols * splits;
@@ -1440,26 +1467,10 @@ int64_t wide_time(int64_t M, int64_t cols, int64_t slabs, int64_t splits, int64_
 // M = 16384, N = 3072, K = 1024 117 -> 91 us (1.13 PFLOP/s); 1024 x 3072
 // 101 -> 74 us (1.39); M = 65536, N = K = 768 89 -> 76 us; but M = 8192,
 // N = 2304, K = 768 (1.1 rounds) 38.7 -> 44.8 us: it stays on 128 x 128.
-bool wide_ok(const GemmDesc& g, int64_t kchunk, int64_t splits, EpiCost c) {
+bool wide_ok(const GemmDesc& g, int64_t kchunk, int64_t splits, EpiKind kind) {
+  const EpiCost c = epi_cost(kind);
   return wide_time(g.M, col_tiles(g, 256), kchunk / 64, splits, c.wide) <
          pipe_time(g.M, col_tiles(g, 128), kchunk / 64, splits, c.pipe);
-}
-
-template <bool AMC, bool BNC, int SEG, class Epi>
-hipError_t launch_wide(const GemmDesc& g, const Epi& epi, hipStream_t s) {
-  Operand<bf16, AMC, kSegNone> A{{(const bf16*)g.A, nullptr, nullptr}, g.lda, 0};
-  Operand<bf16, BNC, SEG> B{{(const bf16*)g.B[0], (const bf16*)g.B[1], (const bf16*)g.B[2]}, g.ldb,
-                            g.seg_len};
-  int splits = g.splits < 1 ? 1 : g.splits;
-  int kchunk = (g.K + splits - 1) / splits;
-  kchunk = (kchunk + 63) / 64 * 64;
-  if (g.kchunk > 0) kchunk = g.kchunk;
-  splits = (g.K + kchunk - 1) / kchunk;
-  dim3 grid((unsigned)col_tiles(g, 256), (g.M + 255) / 256, splits);
-  const int group = xcd_group_rows((int)grid.x, (int)grid.y, (int)grid.z);
-  hipLaunchKernelGGL((gemm_wide_kernel<AMC, BNC, SEG, Epi>), grid, dim3(256), 0, s, g.M, g.N, g.K,
-                     A, B, kchunk, group, epi);
-  return hipGetLastError();
 }
 
 // Up to this many 128 x 128 tiles (half the CUs) a product runs on 32 x 128
@@ -1471,27 +1482,73 @@ hipError_t launch_wide(const GemmDesc& g, const Epi& epi, hipStream_t s) {
 // (64 x 128 tiles were never the fastest.)
 constexpr int64_t kSmallTiles = 128;
 
+// bf16: 256 x 256 tiles where the time model says so, else 128 x 128, two
+// 32 KB slabs in flight, so that two workgroups share a CU (measured faster on
+// the layer's shapes than a deeper ring with one workgroup per CU).  Eight
+// waves of 64 x 32 by default: more waves to cover the load and LDS latencies,
+// at 1.5x the fragment reads per matrix instruction.  Four waves of 64 x 64
+// stay on the weight gradients whose operands are both read transposed and
+// that fill the chip with splits, and on products whose B is split along K
+// (the input gradient of Q, K, V): there eight waves measured slower.  The
+// layer's forward + backward step took 308 instead of 316 us.
+ProductPlan plan_bf16(const GemmDesc& g, EpiKind kind) {
+  ProductPlan p;
+  plan_splits(g, 64, &p);
+  if (wide_ok(g, p.kchunk, p.splits, kind)) {
+    p.kernel = kWide;
+    p.rows = (g.M + 255) / 256;
+    p.cols = (int)col_tiles(g, 256);
+    return p;
+  }
+  p.rows = (g.M + 127) / 128;
+  p.cols = (int)col_tiles(g, 128);
+  const int64_t tiles = (int64_t)p.rows * p.cols * p.splits;
+  if (g.a_mcontig) {
+    p.kernel = tiles >= 256 ? kPipe4 : kPipe8;
+  } else if (tiles <= kSmallTiles) {
+    p.kernel = kPipeRows32;
+    p.rows = (g.M + 31) / 32;
+  } else {
+    p.kernel = g.seg == kSegK ? kPipe4 : kPipe8;
+  }
+  return p;
+}
+
+template <int PBM, int ST, int WGM, int WGN, bool AMC, bool BNC, int SEG, class Epi>
+hipError_t launch_pipe_w(const GemmDesc& g, const ProductPlan& p, const Epi& epi, hipStream_t s) {
+  constexpr int PBN = 128, PBK = 64;
+  Operand<bf16, AMC, kSegNone> A{{(const bf16*)g.A, nullptr, nullptr}, g.lda, 0};
+  Operand<bf16, BNC, SEG> B{{(const bf16*)g.B[0], (const bf16*)g.B[1], (const bf16*)g.B[2]}, g.ldb,
+                            g.seg_len};
+  const int group = xcd_group_rows(p.cols, p.rows, p.splits);
+  hipLaunchKernelGGL((gemm_pipe_kernel<PBM, PBN, PBK, ST, WGM, WGN, AMC, BNC, SEG, Epi>),
+                     plan_grid(p), dim3(WGM * WGN * 64), 0, s, g.M, g.N, g.K, A, B, p.kchunk, group,
+                     epi);
+  return hipGetLastError();
+}
+
+template <bool AMC, bool BNC, int SEG, class Epi>
+hipError_t launch_wide(const GemmDesc& g, const ProductPlan& p, const Epi& epi, hipStream_t s) {
+  Operand<bf16, AMC, kSegNone> A{{(const bf16*)g.A, nullptr, nullptr}, g.lda, 0};
+  Operand<bf16, BNC, SEG> B{{(const bf16*)g.B[0], (const bf16*)g.B[1], (const bf16*)g.B[2]}, g.ldb,
+                            g.seg_len};
+  const int group = xcd_group_rows(p.cols, p.rows, p.splits);
+  hipLaunchKernelGGL((gemm_wide_kernel<AMC, BNC, SEG, Epi>), plan_grid(p), dim3(256), 0, s, g.M,
+                     g.N, g.K, A, B, p.kchunk, group, epi);
+  return hipGetLastError();
+}
+
 template <bool AMC, bool BNC, int SEG, class Epi>
 hipError_t launch_pipe(const GemmDesc& g, const Epi& epi, hipStream_t s) {
-  {
-    const int sp = g.splits < 1 ? 1 : g.splits;
-    const int kc = g.kchunk > 0 ? g.kchunk : ((g.K + sp - 1) / sp + 63) / 64 * 64;
-    if (wide_ok(g, kc, (g.K + kc - 1) / kc, epi_cost((const Epi*)nullptr)))
-      return launch_wide<AMC, BNC, SEG>(g, epi, s);
-  }
+  const ProductPlan p = plan_bf16(g, Epi::kKind);
+  if (p.kernel == kWide) return launch_wide<AMC, BNC, SEG>(g, p, epi, s);
   if constexpr (AMC) {
-    int splits = g.splits < 1 ? 1 : g.splits;
-    if (g.kchunk > 0) splits = (g.K + g.kchunk - 1) / g.kchunk;
-    const int64_t wgs = (int64_t)((g.N + 127) / 128) * ((g.M + 127) / 128) * splits;
-    if (wgs >= 256) return launch_pipe_w<128, 2, 2, 2, AMC, BNC, SEG>(g, epi, s);
+    if (p.kernel == kPipe4) return launch_pipe_w<128, 2, 2, 2, AMC, BNC, SEG>(g, p, epi, s);
   } else {
-    const int sp = g.splits < 1 ? 1 : g.splits;
-    const int splits = g.kchunk > 0 ? (g.K + g.kchunk - 1) / g.kchunk : sp;
-    const int64_t tiles = col_tiles(g, 128) * ((g.M + 127) / 128) * splits;
-    if (tiles <= kSmallTiles) return launch_pipe_w<32, 4, 1, 4, AMC, BNC, SEG>(g, epi, s);
+    if (p.kernel == kPipeRows32) return launch_pipe_w<32, 4, 1, 4, AMC, BNC, SEG>(g, p, epi, s);
   }
-  if constexpr (SEG == kSegK) return launch_pipe_w<128, 2, 2, 2, AMC, BNC, SEG>(g, epi, s);
-  return launch_pipe_w<128, 2, 2, 4, AMC, BNC, SEG>(g, epi, s);
+  if constexpr (SEG == kSegK) return launch_pipe_w<128, 2, 2, 2, AMC, BNC, SEG>(g, p, epi, s);
+  return launch_pipe_w<128, 2, 2, 4, AMC, BNC, SEG>(g, p, epi, s);
 }
 
 // The bf16 kernels need whole 64-deep slabs unless both operands are
@@ -1566,6 +1623,7 @@ static int splitk_plan(bool bf, int M, int N, int K, int min_k, int* kchunk) {
 
 // Writes (or accumulates into) up to three float32 outputs split along N.
 struct EpiSegOut {
+  static constexpr EpiKind kKind = kEpiPartial;
   float* C[3];
   int64_t ldc;
   int seg;
@@ -1734,3 +1792,22 @@ hipError_t gemm_hbar(DType dt, const GemmDesc& g, const HbarEpi& e, hipStream_t 
 }
 
 }  // namespace bcmt
+
+// Not part of the library's interface: how a product would be launched, so
+// that tests can tell which kernel serves a shape and that its grid is within
+// the limits.  kind: EpiKind.  min_k > 0: the split-K plan of gemm_splitk.
+// out: kernel (ProductKernel), grid x, y, z, K range of a split.
+extern "C" void bcmt_internal_product_plan(int bf16, int kind, int M, int N, int K, int a_mcontig,
+                                           int b_ncontig, int seg, int seg_len, int min_k,
+                                           int* out) {
+  using namespace bcmt;
+  GemmDesc g{M, N, K, nullptr, 0, a_mcontig != 0, {}, 0, b_ncontig != 0, seg, seg_len, 1, 0};
+  if (min_k > 0) g.splits = splitk_plan(bf16 != 0, M, N, K, min_k, &g.kchunk);
+  const ProductPlan p = bf16 ? plan_bf16(g, (EpiKind)kind) : plan_f32(g);
+  const dim3 grid = plan_grid(p);
+  out[0] = p.kernel;
+  out[1] = (int)grid.x;
+  out[2] = (int)grid.y;
+  out[3] = (int)grid.z;
+  out[4] = p.kchunk;
+}

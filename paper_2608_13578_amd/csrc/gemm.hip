@@ -96,7 +96,10 @@ template <> struct Raw8<float> {
 
 // What an epilogue reads from memory for 8 columns: pre() requests it and
 // fin8() uses it, so that a caller can keep the requests of several items
-// in flight ahead of the stores of others.
+// in flight ahead of the stores of others (the 256 x 256 kernel).  apply8()
+// does both for one item, in a body of its own: as pre() and fin8() one after
+// the other it was a few instructions longer and the measured layer's step
+// 0.8 % slower (B = 8, T = 1024, D = 768: 302.6 -> 304.9 us).
 template <class Epi, class = void>
 struct HasPre {
   static constexpr bool value = false;
@@ -146,9 +149,17 @@ struct EpiStore {
     st8(c, o);
   }
   __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
-    Pre p;
-    pre(m, n, ok, p);
-    fin8(m, n, v, ok, p);
+    if (!ok) return;
+    float o[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = v[e];
+    if (add) {
+      float a[8];
+      ld8(add + (int64_t)m * ld_add + n, a);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) o[e] += a[e];
+    }
+    st8(C + (int64_t)m * ldc + n, o);
   }
 };
 
@@ -207,9 +218,13 @@ struct EpiGeluBwd {
     st8(dU + (int64_t)m * ld + n, d);
   }
   __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
-    Pre p;
-    pre(m, n, ok, p);
-    fin8(m, n, v, ok, p);
+    if (!ok) return;
+    const int64_t off = (int64_t)m * ld + n;
+    float u[8], d[8];
+    ld8(U + off, u);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) d[k] = v[k] * gelu_grad_f(u[k]);
+    st8(dU + off, d);
   }
 };
 
@@ -340,9 +355,34 @@ struct EpiGate {
     st8(reinterpret_cast<typename GateT<T>::type*>(e.G) + off, g);
   }
   __device__ __forceinline__ void apply8(int m, int n, const float (&u)[8], bool ok) const {
-    Pre p;
-    pre(m, n, ok, p);
-    fin8(m, n, u, ok, p);
+    if (!ok) return;
+    const int b = m / e.T;
+    const int t = m - b * e.T;
+    const int blk = t / e.L;
+    const int64_t off = (int64_t)m * e.D + n;
+    float h[8], c[8], g[8], y[8];
+    ld8(reinterpret_cast<const T*>(e.H) + off, h);
+    if (blk > 0) {
+      ld8(e.P + (int64_t)(b * e.nb + blk - 1) * e.D + n, c);
+    } else if (e.Pc) {
+      ld8(e.Pc + (int64_t)b * e.D + n, c);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) c[k] = 0.f;
+    }
+    if (e.X) {
+      float x[8];
+      ld8(reinterpret_cast<const T*>(e.X) + off, x);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) h[k] += x[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      g[k] = sigmoidf_(u[k]);
+      y[k] = h[k] + g[k] * c[k];
+    }
+    st8(reinterpret_cast<T*>(e.Y) + off, y);
+    st8(reinterpret_cast<typename GateT<T>::type*>(e.G) + off, g);
   }
 };
 
@@ -374,9 +414,19 @@ struct EpiHbar {
     st8(reinterpret_cast<T*>(e.dH) + (int64_t)m * e.D + n, o);
   }
   __device__ __forceinline__ void apply8(int m, int n, const float (&v)[8], bool ok) const {
-    Pre p;
-    pre(m, n, ok, p);
-    fin8(m, n, v, ok, p);
+    if (!ok) return;
+    const int b = m / e.T;
+    const int t = m - b * e.T;
+    const int blk = t / e.L;
+    const int64_t off = (int64_t)m * e.D + n;
+    float dy[8], dS[8], w[8], o[8];
+    ld8(reinterpret_cast<const T*>(e.dY) + off, dy);
+    ld8(e.dS + (int64_t)(b * e.nb + blk) * e.D + n, dS);
+    ld8(reinterpret_cast<const T*>(e.wp) + n, w);
+    const float a = e.a[m], ds = e.ds[m];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) o[k] = v[k] + dy[k] + a * dS[k] + ds * w[k];
+    st8(reinterpret_cast<T*>(e.dH) + off, o);
   }
 };
 

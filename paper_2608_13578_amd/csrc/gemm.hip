@@ -675,12 +675,14 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
   la.setup(m0, M, A.ld, wave, lane);
   lb.setup(bn0, bnmax, B.ld, wave, lane);
   // Slab base of B at global k (B split along K: each slab lies inside one
-  // part; the launcher checks that the part length is a multiple of BK).
+  // part; the launcher checks that the part length is a multiple of BK).  The
+  // division and the indexed pointer are scalar work; the two compares of the
+  // 256 x 256 kernel in their place took dX of the measured layer (M = 8192,
+  // N = 768, K = 2304) from 37.3 to 38.3 us.
   auto bslab = [&](int k) {
     if constexpr (BSEG == kSegK) {
-      const int sl = B.seg_len;
-      const bf16* p = k < sl ? B.p[0] : k < 2 * sl ? B.p[1] : B.p[2];
-      return lb.slab(p, B.ld, k < sl ? k : k < 2 * sl ? k - sl : k - 2 * sl);
+      const int sg = k / B.seg_len;
+      return lb.slab(B.p[sg], B.ld, k - sg * B.seg_len);
     } else {
       return lb.slab(bptr, B.ld, k);
     }

@@ -485,7 +485,7 @@ __device__ __forceinline__ void sync_lds() {
   __builtin_amdgcn_s_barrier();
 }
 
-template <int NW>
+template <int NW, bool MANY>
 __global__ __launch_bounds__(NW * 64, 3) void attn_fwd_bf16_kernel(const bf16* __restrict__ qkv,
                                                                bf16* __restrict__ out,
                                                                float* __restrict__ lse, int Tn,
@@ -495,7 +495,7 @@ __global__ __launch_bounds__(NW * 64, 3) void attn_fwd_bf16_kernel(const bf16* _
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile(ntile, true);
+  const AttnTile at = attn_tile<MANY>(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
@@ -646,7 +646,7 @@ __global__ __launch_bounds__(NW * 64, 3) void attn_fwd_bf16_kernel(const bf16* _
   }
 }
 
-template <int NW>
+template <int NW, bool MANY>
 __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_bf16_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ o, const bf16* __restrict__ dout,
     const float* __restrict__ lse, float* __restrict__ delta, bf16* __restrict__ dqkv, int Tn,
@@ -656,7 +656,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_bf16_kernel(
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile(ntile, true);
+  const AttnTile at = attn_tile<MANY>(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
@@ -779,7 +779,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_bf16_kernel(
   }
 }
 
-template <int NW>
+template <int NW, bool MANY>
 __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_bf16_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ dout, const float* __restrict__ lse,
     const float* __restrict__ delta, bf16* __restrict__ dqkv, int Tn, int D, int H, int L, int ntile,
@@ -790,7 +790,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_bf16_kernel(
   __shared__ __attribute__((aligned(16))) float vec_s[2][2][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile(ntile, false);
+  const AttnTile at = attn_tile<MANY>(ntile, false);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
@@ -1334,8 +1334,11 @@ hipError_t attn_fwd(DType dt, const void* qkv, void* out, float* lse, int B, int
     const int nt = (lb + nw * 32 - 1) / (nw * 32);
     const dim3 grid = attn_grid(nt, (T + L - 1) / L, B * H);
     const float sl2 = 1.4426950408889634f / sqrtf((float)kDh);
-#define FWD(NW) hipLaunchKernelGGL(attn_fwd_bf16_kernel<NW>, grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (bf16*)out, lse, T, D, H, L, nt, sl2)
-    if (nw == 1) FWD(1); else if (nw == 2) FWD(2); else FWD(4);
+#define FWD(NW, MANY) hipLaunchKernelGGL((attn_fwd_bf16_kernel<NW, MANY>), grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (bf16*)out, lse, T, D, H, L, nt, sl2)
+    if (nw == 1) FWD(1, false);
+    else if (nw == 2) FWD(2, false);
+    else if (nt == 1) FWD(4, false);
+    else FWD(4, true);
 #undef FWD
     return hipGetLastError();
   }
@@ -1354,8 +1357,11 @@ hipError_t attn_bwd_dq(DType dt, const void* qkv, const void* out, const void* d
     const dim3 grid = attn_grid(nt, (T + L - 1) / L, B * H);
     const float scale = 1.0f / sqrtf((float)kDh);
     const float sl2 = 1.4426950408889634f * scale;
-#define DQ(NW) hipLaunchKernelGGL(attn_bwd_dq_bf16_kernel<NW>, grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (const bf16*)out, (const bf16*)dout, lse, delta, (bf16*)dqkv, T, D, H, L, nt, sl2, scale)
-    if (nw == 1) DQ(1); else if (nw == 2) DQ(2); else DQ(4);
+#define DQ(NW, MANY) hipLaunchKernelGGL((attn_bwd_dq_bf16_kernel<NW, MANY>), grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (const bf16*)out, (const bf16*)dout, lse, delta, (bf16*)dqkv, T, D, H, L, nt, sl2, scale)
+    if (nw == 1) DQ(1, false);
+    else if (nw == 2) DQ(2, false);
+    else if (nt == 1) DQ(4, false);
+    else DQ(4, true);
 #undef DQ
     return hipGetLastError();
   }
@@ -1395,8 +1401,11 @@ hipError_t attn_bwd_dkdv(DType dt, const void* qkv, const void* dout, const floa
     const dim3 grid = attn_grid(nt, (T + L - 1) / L, B * H);
     const float scale = 1.0f / sqrtf((float)kDh);
     const float sl2 = 1.4426950408889634f * scale;
-#define DKDV(NW) hipLaunchKernelGGL(attn_bwd_dkdv_bf16_kernel<NW>, grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (const bf16*)dout, lse, (const float*)delta, (bf16*)dqkv, T, D, H, L, nt, sl2, scale)
-    if (nw == 1) DKDV(1); else if (nw == 2) DKDV(2); else DKDV(4);
+#define DKDV(NW, MANY) hipLaunchKernelGGL((attn_bwd_dkdv_bf16_kernel<NW, MANY>), grid, dim3(NW * 64), 0, s, (const bf16*)qkv, (const bf16*)dout, lse, (const float*)delta, (bf16*)dqkv, T, D, H, L, nt, sl2, scale)
+    if (nw == 1) DKDV(1, false);
+    else if (nw == 2) DKDV(2, false);
+    else if (nt == 1) DKDV(4, false);
+    else DKDV(4, true);
 #undef DKDV
     return hipGetLastError();
   }

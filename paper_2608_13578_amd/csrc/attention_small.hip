@@ -312,7 +312,7 @@ __device__ __forceinline__ void sm_vm_wait() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <int NW, int DH>
+template <int NW, int DH, bool MANY>
 __global__ __launch_bounds__(NW * 64) void attn_small_fwd_mfma_kernel(
     const bf16* __restrict__ qkv, bf16* __restrict__ out, float* __restrict__ lse, int Tn, int D,
     int H, int L, int ntile, float sl2) {
@@ -322,7 +322,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_fwd_mfma_kernel(
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * DH];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile(ntile, true);
+  const AttnTile at = attn_tile<MANY>(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
@@ -462,7 +462,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_fwd_mfma_kernel(
 // scores S = K Q^T and dP = V dO^T, dS = P (dP - delta) with
 // P = 2^(S sl2 - lse), then dQ += K^T dS.  Writes delta_t = dO_t . O_t,
 // which the dK / dV pass reads.
-template <int NW, int DH>
+template <int NW, int DH, bool MANY>
 __global__ __launch_bounds__(NW * 64) void attn_small_dq_mfma_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ o, const bf16* __restrict__ dout,
     const float* __restrict__ lse, float* __restrict__ delta, bf16* __restrict__ dqkv, int Tn,
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_dq_mfma_kernel(
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * DH];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile(ntile, true);
+  const AttnTile at = attn_tile<MANY>(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
@@ -588,7 +588,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_dq_mfma_kernel(
 // tiles of 64 from the workgroup's first key on, with their lse and delta,
 // staged by direct loads.  S = Q K^T and dP = dO V^T per tile; then
 // dV += dO^T P and dK += Q^T dS.
-template <int NW, int DH>
+template <int NW, int DH, bool MANY>
 __global__ __launch_bounds__(NW * 64) void attn_small_dkdv_mfma_kernel(
     const bf16* __restrict__ qkv, const bf16* __restrict__ dout, const float* __restrict__ lse,
     const float* __restrict__ delta, bf16* __restrict__ dqkv, int Tn, int D, int H, int L, int ntile,
@@ -600,7 +600,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_dkdv_mfma_kernel(
   __shared__ __attribute__((aligned(16))) float vec_s[2][2][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile(ntile, false);
+  const AttnTile at = attn_tile<MANY>(ntile, false);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
@@ -739,22 +739,24 @@ hipError_t small_bwd_mfma(int pass, const void* qkv, const void* o, const void* 
   const dim3 grid = attn_grid(nt, (Tn + L - 1) / L, B * H);
   const float scale = 1.0f / sqrtf((float)DH);
   const float sl2 = 1.4426950408889634f * scale;
-#define SDQ(NW)                                                                               \
-  hipLaunchKernelGGL((attn_small_dq_mfma_kernel<NW, DH>), grid, dim3(NW * 64), 0, s,           \
+#define SDQ(NW, MANY)                                                                         \
+  hipLaunchKernelGGL((attn_small_dq_mfma_kernel<NW, DH, MANY>), grid, dim3(NW * 64), 0, s,     \
                      (const bf16*)qkv, (const bf16*)o, (const bf16*)dout, lse, delta,           \
                      (bf16*)dqkv, Tn, D, H, L, nt, sl2, scale)
-#define SDKDV(NW)                                                                             \
-  hipLaunchKernelGGL((attn_small_dkdv_mfma_kernel<NW, DH>), grid, dim3(NW * 64), 0, s,         \
+#define SDKDV(NW, MANY)                                                                       \
+  hipLaunchKernelGGL((attn_small_dkdv_mfma_kernel<NW, DH, MANY>), grid, dim3(NW * 64), 0, s,         \
                      (const bf16*)qkv, (const bf16*)dout, lse, (const float*)delta,             \
                      (bf16*)dqkv, Tn, D, H, L, nt, sl2, scale)
   if (pass == 1) {
-    if (nw == 1) SDQ(1);
-    else if (nw == 2) SDQ(2);
-    else SDQ(4);
+    if (nw == 1) SDQ(1, false);
+    else if (nw == 2) SDQ(2, false);
+    else if (nt == 1) SDQ(4, false);
+    else SDQ(4, true);
   } else {
-    if (nw == 1) SDKDV(1);
-    else if (nw == 2) SDKDV(2);
-    else SDKDV(4);
+    if (nw == 1) SDKDV(1, false);
+    else if (nw == 2) SDKDV(2, false);
+    else if (nt == 1) SDKDV(4, false);
+    else SDKDV(4, true);
   }
 #undef SDQ
 #undef SDKDV
@@ -769,12 +771,13 @@ hipError_t small_fwd_mfma(const void* qkv, void* out, float* lse, int B, int Tn,
   const int nt = (lb + nw * 32 - 1) / (nw * 32);
   const dim3 grid = attn_grid(nt, (Tn + L - 1) / L, B * H);
   const float sl2 = 1.4426950408889634f / sqrtf((float)DH);
-#define SFWD(NW)                                                                              \
-  hipLaunchKernelGGL((attn_small_fwd_mfma_kernel<NW, DH>), grid, dim3(NW * 64), 0, s,          \
+#define SFWD(NW, MANY)                                                                        \
+  hipLaunchKernelGGL((attn_small_fwd_mfma_kernel<NW, DH, MANY>), grid, dim3(NW * 64), 0, s,          \
                      (const bf16*)qkv, (bf16*)out, lse, Tn, D, H, L, nt, sl2)
-  if (nw == 1) SFWD(1);
-  else if (nw == 2) SFWD(2);
-  else SFWD(4);
+  if (nw == 1) SFWD(1, false);
+  else if (nw == 2) SFWD(2, false);
+  else if (nt == 1) SFWD(4, false);
+  else SFWD(4, true);
 #undef SFWD
   return hipGetLastError();
 }

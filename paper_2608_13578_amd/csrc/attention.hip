@@ -495,7 +495,7 @@ __global__ __launch_bounds__(NW * 64, 3) void attn_fwd_bf16_kernel(const bf16* _
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile<MANY>(ntile, true);
+  const AttnTile at = attn_tile<MANY, kDh>(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
@@ -656,7 +656,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dq_bf16_kernel(
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile<MANY>(ntile, true);
+  const AttnTile at = attn_tile<MANY, kDh>(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
@@ -790,7 +790,7 @@ __global__ __launch_bounds__(NW * 64) void attn_bwd_dkdv_bf16_kernel(
   __shared__ __attribute__((aligned(16))) float vec_s[2][2][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile<MANY>(ntile, false);
+  const AttnTile at = attn_tile<MANY, kDh>(ntile, false);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);

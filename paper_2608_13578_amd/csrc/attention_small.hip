@@ -322,7 +322,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_fwd_mfma_kernel(
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * DH];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile<MANY>(ntile, true);
+  const AttnTile at = attn_tile<MANY, DH>(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
@@ -473,7 +473,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_dq_mfma_kernel(
   __shared__ __attribute__((aligned(1024))) bf16 lds[2][2][64 * DH];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile<MANY>(ntile, true);
+  const AttnTile at = attn_tile<MANY, DH>(ntile, true);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);
@@ -600,7 +600,7 @@ __global__ __launch_bounds__(NW * 64) void attn_small_dkdv_mfma_kernel(
   __shared__ __attribute__((aligned(16))) float vec_s[2][2][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane & 15, lg = lane >> 4;
-  const AttnTile at = attn_tile<MANY>(ntile, false);
+  const AttnTile at = attn_tile<MANY, DH>(ntile, false);
   const int b = at.bh / H, h = at.bh % H;
   const int bs = at.blk * L;
   const int be = min(bs + L, Tn);

@@ -7,7 +7,11 @@ Bounds as in test_gpu_parity, the decay gradient apart where it is a small
 sum of large terms (-0.0077 and -0.017 over three blocks): there 1.25 times
 the largest error of the rounding model (bf16_model.py, 12 realisations:
 0.356 and 0.135; at most 2.9e-3 on the other cases, and 6.7e-3 on every other
-output).
+output).  The same two blockings run again on inputs whose decay gradient does
+not cancel (-0.76 and -0.80; the model errs by at most 2.1e-3).
+
+Heads narrower than a 128-byte line are dealt to the XCDs in eighths where
+sequence x head is a multiple of 8: several heads per XCD, in both widths.
 """
 
 import pytest
@@ -19,17 +23,22 @@ from test_gpu_parity import inputs, run_gpu, run_oracle, say, torch_cuda  # noqa
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,T,D,H,L,decay_bound", [
+@pytest.mark.parametrize("case", [
     (3, 300, 192, 3, 129, 2e-2),  # heads of 64: blocks of 129, 129 and 42 (fused backward)
     (1, 700, 192, 3, 300, 0.45),  # blocks of 300, 300 and 100 (two-kernel backward)
     (3, 300, 64, 4, 129, 2e-2),   # heads of 16
     (1, 700, 192, 6, 300, 0.17),  # heads of 32
+    (1, 700, 192, 3, 300, 2e-2, 2),
+    (1, 700, 192, 6, 300, 2e-2, 2),
+    (4, 300, 128, 8, 129, 2e-2),   # heads of 16, 32 sequence x heads
+    (4, 700, 128, 4, 300, 2e-2),   # heads of 32, 16 sequence x heads
     (2, 5500, 192, 3, 129, 2e-2),  # 43 blocks of two tiles in groups of 22: one past the end
     (2, 4200, 64, 4, 129, 2e-2),   # the same in every pass: 33 blocks in groups of 17
 ])
-def test_several_tiles(torch_cuda, B, T, D, H, L, decay_bound):  # noqa: F811
+def test_several_tiles(torch_cuda, case):  # noqa: F811
+    B, T, D, H, L, decay_bound, *seed = case
     say(f"case B={B} T={T} D={D} H={H} L={L}")
-    X, W, dY = inputs(B, T, D, "bf16", w_std=0.05)
+    X, W, dY = inputs(B, T, D, "bf16", seed=seed[0] if seed else 0, w_std=0.05)
     gpu = run_gpu(torch_cuda, B, T, D, H, L, "bf16", X, W, dY)
     for k, ref in run_oracle(B, T, D, H, L, X, W, dY).items():
         if k == "dgamma":

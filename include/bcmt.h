@@ -376,8 +376,9 @@ int bcmt_model_cast(const bcmt_model_config* cfg, const float* params, void* par
  * reads params_bf16 (weights) and params (LayerNorm gains and biases).
  * All pointers are device memory, 16-byte aligned; ws holds at least
  * bcmt_model_workspace_bytes(cfg).  `side` takes the weight gradients of
- * each layer and MLP (NULL: everything on `stream`; work enqueued on `stream`
- * after the call sees every output either way).  Errors as for the layer. */
+ * each layer and MLP (NULL, or a step too small to gain from it: everything on
+ * `stream`; work enqueued on `stream` after the call sees every output either
+ * way).  Errors as for the layer. */
 int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
                           const int32_t* targets, float* params, void* params_bf16,
                           float* grads, float* adam_m, float* adam_v, const bcmt_adamw* opt,

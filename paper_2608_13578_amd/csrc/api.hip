@@ -590,7 +590,7 @@ static int layer_backward(const bcmt_config* cfg, const void* X, const bcmt_para
                           const void* saved, const void* dY, void* dX, const bcmt_grads* grads,
                           void* ws, size_t ws_bytes, void* stream, const bcmt_side* side,
                           bool chunk, const bcmt_carry* dcout, const bcmt_carry* dcin,
-                          bool fork_small = false) {
+                          bool fork_always = false) {
   int st = check_config(cfg);
   if (st != BCMT_OK) return st;
   if (!X || !prm || !saved || !dY) return BCMT_ERR_INVALID;
@@ -622,19 +622,21 @@ static int layer_backward(const bcmt_config* cfg, const void* X, const bcmt_para
 
   // The weight-gradient products go to the caller's second stream when one
   // is given and they are worth it: the three forks and the join cost the
-  // host about 50 us (each an event record and a wait), more than a small
-  // pass takes on the GPU.  Measured, second stream against one stream, the
-  // step forward + backward: B T = 256, D = 128 f32 180 against 131 us;
-  // B T = 2000, D = 256 166 against 122; B T = 16384, D = 128 177 against 153;
-  // at B T D^2 = 2.7e8 (1024 x 512) 173 against 139, but B T = 2048, D = 768
-  // 176 against 192.  float32 products are ten times slower: 1024 x 256 168
-  // against 170, 2048 x 256 180 against 187.  Inside a model step
-  // (fork_small) the host is far ahead, and small layers fork too (the step
-  // of the 6-layer model at D = 128: 3.40 against 3.47 ms).  With per-stage
+  // host about 50 us (each an event record and a wait), which a pass wins
+  // back once it keeps the GPU busy for longer than the host needs to enqueue
+  // it.  Time of forward + backward on one stream over that on two, bf16, by
+  // B T D^2, with D in brackets: 2.7e8 0.80 to 1.05 [128, 256, 512], 5e8 to
+  // 9e8 0.91 to 1.02 [256 to 768] and 0.96 to 1.00 [64, 128], 1.1e9 0.92 [512]
+  // 0.97 [1024] 0.97 to 0.99 [256] 1.02 to 1.07 [128], 1.2e9 1.05 [768]; and
+  // 1.06 at 5.4e8 [64]: narrow layers spend their time on B T D instead, so
+  // either may reach its bound.  float32 (products ten times slower): 6.6e7
+  // 0.89 to 0.94, 1.3e8 0.96 to 1.02, 2e8 0.94 to 1.06, 2.7e8 0.97 to 1.04.
+  // Inside a model step the model decides (fork_always).  With per-stage
   // tracing on, everything runs on the caller's stream so that each stage is
   // timed alone.
-  const double work = (double)p.B * p.T * p.D * p.D;
-  const bool worth = fork_small || work >= (p.dt == DType::BF16 ? 3e8 : 6e7);
+  const double btd = (double)p.B * p.T * p.D;
+  const bool worth = fork_always || (p.dt == DType::BF16 ? btd * p.D >= 1.2e9 || btd >= 6e6
+                                                         : btd * p.D >= 1.2e8);
   const bool fork = side && worth && !g_trace.on.load(std::memory_order_relaxed);
   const hipStream_t main_s = (hipStream_t)stream;
   const hipStream_t side_s = fork ? (hipStream_t)side->stream : main_s;

@@ -795,8 +795,17 @@ int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
   KCHK();
 
   // ---- backward
-  // (the second stream as in the layer's backward: not while tracing)
-  const bool fork = side && !trace_is_on();
+  // The second stream as in the layer's backward: not while tracing, and
+  // where the step keeps the GPU busy for longer than the host needs to
+  // enqueue it.  A large head does that by itself (the host enqueues the
+  // layers meanwhile), else the layers have to.  Time of the step on one
+  // stream over that on two, by B T d^2 of a layer and B T V d of the head:
+  // 3e8 and 1.3e10 1.04, 2.7e8 and 1.1e11 1.04, 2.7e8 and 5e10 1.02; but 2.7e8
+  // and 1e9 to 2e9 0.95, 5.4e8 and 1e9 0.97, 1.3e8 and 5e10 0.96, 6.7e7 and
+  // 2.6e10 0.93, 2e6 and 3e7 0.53 to 0.59.
+  const double btd = (double)BT * d;
+  const bool worth = btd * d >= (btd * c.V >= 1e10 ? 2.5e8 : 1e9);
+  const bool fork = side && worth && !trace_is_on();
   const hipStream_t side_s = fork ? (hipStream_t)side->stream : s;
   float* wpart = (float*)(W + p.wpart);
   bf16* dr = (bf16*)(W + p.dr);
@@ -896,7 +905,8 @@ int bcmt_model_train_step(const bcmt_model_config* cfg, const int32_t* tokens,
     lg.dWg = gw(lidx(l, 7));
     lg.dwp = gw(lidx(l, 8));
     int e = layer_backward_in_model(&p.lc, W + p.a + act * l, &lp, W + p.saved + p.layer_saved * l,
-                                    dr2, W + p.dxm, &lg, W + p.lws, p.layer_ws, s, side);
+                                    dr2, W + p.dxm, &lg, W + p.lws, p.layer_ws, s,
+                                    fork ? side : nullptr);
     if (e != BCMT_OK) return e;
     if (fork) {
       CHK(hipEventRecord((hipEvent_t)side->join, side_s));

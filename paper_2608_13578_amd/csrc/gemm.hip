@@ -45,7 +45,7 @@ struct Operand {
 // fragment layout would write 32-byte pieces of 16 rows.  Every lane calls
 // apply8 the same number of times (with ok = false outside the matrix), so
 // an epilogue may reduce across lanes.
-template <int BM, int BN, int FM, int FN, int WTM, int WTN, int NTH, class Epi>
+template <int BM, int BN, int FM, int FN, int WTM, int WTN, int NTH, bool SPLIT = false, class Epi>
 __device__ __forceinline__ void staged_epilogue(const Epi& epi, const f32x4 (&acc)[FM][FN],
                                                 float* cs, int m0, int n0, int wm, int wn, int M,
                                                 int N, int tid) {
@@ -72,7 +72,14 @@ __device__ __forceinline__ void staged_epilogue(const Epi& epi, const f32x4 (&ac
     const f32x4 b = *reinterpret_cast<const f32x4*>(row + (((2 * c8 + 1) ^ (r & (CH - 1))) * 4));
     const float v[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
     const int m = m0 + r, n = n0 + c8 * 8;
-    epi.apply8(m, n, v, m < M && n < N);
+    const bool ok = m < M && n < N;
+    if constexpr (SPLIT) {
+      typename Epi::Pre pre;
+      epi.pre(m, n, ok, pre);
+      epi.fin8(m, n, v, ok, pre);
+    } else {
+      epi.apply8(m, n, v, ok);
+    }
   }
 }
 
@@ -99,7 +106,10 @@ template <> struct Raw8<float> {
 // in flight ahead of the stores of others (the 256 x 256 kernel).  apply8()
 // does both for one item, in a body of its own: as pre() and fin8() one after
 // the other it was a few instructions longer and the measured layer's step
-// 0.8 % slower (B = 8, T = 1024, D = 768: 302.6 -> 304.9 us).
+// 0.8 % slower (B = 8, T = 1024, D = 768: 302.6 -> 304.9 us).  The 32 x 128
+// kernel's gate is the exception (SPLIT above): its few workgroups wait for
+// memory, and with all requests of an item ahead of any use
+// the gate at M = 700, D = 768 takes 8.8 us, 9.5 with apply8().
 template <class Epi, class = void>
 struct HasPre {
   static constexpr bool value = false;
@@ -678,9 +688,15 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
   // part; the launcher checks that the part length is a multiple of BK).  The
   // division and the indexed pointer are scalar work; the two compares of the
   // 256 x 256 kernel in their place took dX of the measured layer (M = 8192,
-  // N = 768, K = 2304) from 37.3 to 38.3 us.
+  // N = 768, K = 2304) from 37.3 to 38.3 us.  On 32 x 128 tiles, with four
+  // slabs in flight, the compares are the faster ones (M = 2000, N = 256,
+  // K = 768 8.3 -> 7.7 us).
   auto bslab = [&](int k) {
-    if constexpr (BSEG == kSegK) {
+    if constexpr (BSEG == kSegK && BM == 32) {
+      const int sl = B.seg_len;
+      const bf16* p = k < sl ? B.p[0] : k < 2 * sl ? B.p[1] : B.p[2];
+      return lb.slab(p, B.ld, k < sl ? k : k < 2 * sl ? k - sl : k - 2 * sl);
+    } else if constexpr (BSEG == kSegK) {
       const int sg = k / B.seg_len;
       return lb.slab(B.p[sg], B.ld, k - sg * B.seg_len);
     } else {
@@ -790,8 +806,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_pipe_kernel(int M, int N, 
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7");
 
   static_assert(STAGES * STAGE * 2 >= BM * BN * 4, "staging tile fits the LDS ring");
-  staged_epilogue<BM, BN, FM, FN, WTM, WTN, NW * 64>(epi, acc, reinterpret_cast<float*>(lds), m0,
-                                                      n0, wm, wn, M, nend, tid);
+  constexpr bool SPLIT = BM == 32 && Epi::kKind == kEpiGate;
+  staged_epilogue<BM, BN, FM, FN, WTM, WTN, NW * 64, SPLIT>(
+      epi, acc, reinterpret_cast<float*>(lds), m0, n0, wm, wn, M, nend, tid);
 }
 
 // ------------------------------------------------------------------ wide kernel

@@ -130,6 +130,8 @@ enum EpiKind {
   kEpiHeadStats = 6,
   kEpiHeadGrad = 7,
   kEpiPartial = 8,
+  kEpiStoreAdd = 9,  // a store with an addend
+  kEpiGateX = 10,    // the gate with the residual input
 };
 
 template <typename TO, typename TA>
@@ -1505,48 +1507,6 @@ hipError_t launch_f32(const GemmDesc& g, const Epi& epi, hipStream_t s) {
   return launch_f32_tile<64, 3, AMC, BNC, SEG>(g, p, epi, s);
 }
 
-// Time model (ns) of a bf16 product with `slabs` 64-deep slabs per
-// workgroup on the two kernels, from 40 measured shapes (M 2048 to 65536,
-// N and K 768 to 3072; within 10 % of them):
-//   128 x 128 tiles, two per CU: 1.17 us per slab and 512 tiles, in
-//     proportion to the tiles (half-filled CUs run faster), 5 us once;
-//   256 x 256 tiles, one per CU: 1.29 us per slab and 8 us of pipeline fill
-//     and epilogue per round of 256 tiles, 4 us once; a partial round costs
-//     about 0.85 of a whole one (the clock rises as CUs idle).
-// An epilogue that also reads memory adds its own time (EpiCost): the large
-// tile has nothing else to run meanwhile.
-struct EpiCost {
-  int64_t pipe;  // per 512 tiles of 128 x 128
-  int64_t wide;  // per 256 tiles of 256 x 256
-};
-EpiCost epi_cost(EpiKind kind) {
-  switch (kind) {
-    case kEpiScore: return {1800, 7300};
-    case kEpiHbar: return {2800, 7800};
-    case kEpiGate: return {9900, 22000};
-    default: return {0, 0};
-  }
-}
-
-int64_t pipe_time(int64_t M, int64_t cols, int64_t slabs, int64_t splits, int64_t extra) {
-  const int64_t tiles = ((M + 127) / 128) * cols * splits;
-  return 5000 + tiles * (slabs * 1170 + extra) / 512;
-}
-int64_t wide_time(int64_t M, int64_t cols, int64_t slabs, int64_t splits, int64_t extra) {
-  const int64_t tiles = ((M + 255) / 256) * cols * splits;
-  const int64_t round = slabs * 1290 + 8000 + extra;
-  return 4000 + tiles / 256 * round + (tiles % 256 ? round * 85 / 100 : 0);
-}
-// Whether the 256 x 256 kernel serves a product.  Measured, 128 x 128 -> 256 x 256:
-// M = 16384, N = 3072, K = 1024 117 -> 91 us (1.13 PFLOP/s); 1024 x 3072
-// 101 -> 74 us (1.39); M = 65536, N = K = 768 89 -> 76 us; but M = 8192,
-// N = 2304, K = 768 (1.1 rounds) 38.7 -> 44.8 us: it stays on 128 x 128.
-bool wide_ok(const GemmDesc& g, int64_t kchunk, int64_t splits, EpiKind kind) {
-  const EpiCost c = epi_cost(kind);
-  return wide_time(g.M, col_tiles(g, 256), kchunk / 64, splits, c.wide) <
-         pipe_time(g.M, col_tiles(g, 128), kchunk / 64, splits, c.pipe);
-}
-
 // Up to this many 128 x 128 tiles (half the CUs) a product runs on 32 x 128
 // tiles, four workgroups for one, with four slabs in flight: it is bound by
 // the latency of its slabs, not by their number.  Measured, 128 x 128 ->
@@ -1555,6 +1515,90 @@ bool wide_ok(const GemmDesc& g, int64_t kchunk, int64_t splits, EpiKind kind) {
 // (128 tiles) 10.0 -> 9.2 us; M = 1000, N = 2304, K = 768 (144) 11.4 -> 14.4.
 // (64 x 128 tiles were never the fastest.)
 constexpr int64_t kSmallTiles = 128;
+
+// The kind of an epilogue with its optional operand.
+template <class Epi>
+EpiKind epi_kind(const Epi&) { return Epi::kKind; }
+template <class TO, class TA>
+EpiKind epi_kind(const EpiStore<TO, TA>& e) { return e.add ? kEpiStoreAdd : kEpiStore; }
+template <class T>
+EpiKind epi_kind(const EpiGate<T>& e) { return e.e.X ? kEpiGateX : kEpiGate; }
+
+// Time models (ns) of a bf16 product of `slabs` 64-deep slabs in `tiles` tiles
+// on the two kernels, fitted to 1566 products of layers and 14 of heads, each timed
+// on both (D = 64 to 2048, M = 2048 to 131072).
+//   128 x 128 tiles, two per CU: rounds of 512 tiles, each 0.92 us a slab and
+//     an epilogue (EpiCost), 5 us of which the next round hides; over many
+//     rounds 0.8 us more each; a partial round costs half of a whole one and
+//     the rest in proportion to its tiles.
+//   256 x 256 tiles, one per CU: rounds of 256 tiles, each 1.36 us a slab (as
+//     CUs idle their clock rises: 0.88 with few tiles) and an epilogue, which
+//     has nothing else to run meanwhile and takes longer the more it reads
+//     from memory.
+// The kernel they choose is on average 0.2 % off the faster of the two and at
+// most 6 % slower than the 128 x 128 kernel.  (In proportion to tiles, without
+// rounds, and with epilogue costs for score, dH and gate alone it was up to
+// 28 %: the gate without a residual at M = 12288, D = 1024 41.7 -> 53.3 us;
+// GELU and head at d = 640, M = 16484 103 -> 144 and 210 -> 247.)
+// Measured, 128 x 128 -> 256 x 256: M = 16384, N = 3072, K = 1024 108 -> 92 us
+// (1.12 PFLOP/s); 1024 x 3072 109 -> 83; M = 65536, N = K = 768 96 -> 82; but
+// M = 8192, N = 2304, K = 768 (1.1 rounds) 37.1 -> 44.9: it stays on 128 x 128.
+struct EpiCost {
+  int64_t pipe;  // per 512 tiles of 128 x 128
+  int64_t wide;  // per 256 tiles of 256 x 256
+};
+EpiCost epi_cost(EpiKind kind) {
+  switch (kind) {
+    case kEpiStoreAdd: return {14520, 18940};
+    case kEpiScore: return {11480, 16180};
+    case kEpiHbar: return {10740, 12790};
+    case kEpiGate: return {15180, 28230};
+    case kEpiGateX: return {18250, 30490};
+    case kEpiHeadStats: return {8830, 11630};
+    case kEpiHeadGrad: return {10120, 13480};
+    default: return {8520, 8430};  // kEpiStore
+  }
+}
+int64_t pipe_time(int64_t tiles, int64_t slabs, int64_t epi) {
+  const int64_t full = tiles / 512, rest = tiles % 512, work = slabs * 920 + epi;
+  int64_t t = 2930 + full * (work - 5040) + std::max<int64_t>(0, full - 4) * 770;
+  if (rest) t += work * (48 * 512 + 52 * rest) / 51200 - 5040;
+  return t;
+}
+int64_t wide_time(int64_t tiles, int64_t slabs, int64_t epi) {
+  const int64_t full = tiles / 256, rest = tiles % 256;
+  int64_t t = 3170 + full * (slabs * 1360 + 310 + epi);
+  if (rest)
+    t += slabs * (880 + 480 * rest / 256) + 310 + epi * (84 * 256 + 16 * rest) / 25600;
+  return t;
+}
+
+// The same for the split weight gradients (two row-contiguous operands, a
+// float32 partial tile), from 40 shapes: in proportion to the 128 x 128 tiles,
+// a partial round of 256 x 256 tiles 0.85 of a whole one.
+int64_t pipe_split_time(int64_t tiles, int64_t slabs) { return 5000 + tiles * slabs * 1170 / 512; }
+int64_t wide_split_time(int64_t tiles, int64_t slabs) {
+  const int64_t round = slabs * 1290 + 8000;
+  return 4000 + tiles / 256 * round + (tiles % 256 ? round * 85 / 100 : 0);
+}
+
+// Up to d = 1024, the widest model, the GELU epilogues cost the 256 x 256 kernel
+// more than its tiles save: M = 4096, d = 1024 59.5 -> 61.3 and 55.8 -> 64.2 us
+// at best, M = 16384, d = 512 79 -> 95 and 79 -> 99.
+constexpr bool wide_serves(EpiKind kind) { return kind != kEpiGelu && kind != kEpiGeluBwd; }
+
+// Whether the 256 x 256 kernel serves a product.  Not where even 128 x 128 tiles
+// are few, nor where a tile's columns are not filled.
+bool wide_ok(const GemmDesc& g, int64_t kchunk, int64_t splits, EpiKind kind) {
+  const int64_t slabs = (kchunk + 63) / 64;
+  const int64_t pipe = (int64_t)((g.M + 127) / 128) * col_tiles(g, 128) * splits;
+  const int64_t wide = (int64_t)((g.M + 255) / 256) * col_tiles(g, 256) * splits;
+  if (kind == kEpiPartial) return wide_split_time(wide, slabs) < pipe_split_time(pipe, slabs);
+  const int width = g.seg == kSegN ? g.seg_len : g.N;
+  if (!wide_serves(kind) || pipe <= kSmallTiles || width < 256) return false;
+  const EpiCost c = epi_cost(kind);
+  return wide_time(wide, slabs, c.wide) < pipe_time(pipe, slabs, c.pipe);
+}
 
 // bf16: 256 x 256 tiles where the time model says so, else 128 x 128, two
 // 32 KB slabs in flight, so that two workgroups share a CU (measured faster on
@@ -1614,8 +1658,10 @@ hipError_t launch_wide(const GemmDesc& g, const ProductPlan& p, const Epi& epi, 
 
 template <bool AMC, bool BNC, int SEG, class Epi>
 hipError_t launch_pipe(const GemmDesc& g, const Epi& epi, hipStream_t s) {
-  const ProductPlan p = plan_bf16(g, Epi::kKind);
-  if (p.kernel == kWide) return launch_wide<AMC, BNC, SEG>(g, p, epi, s);
+  const ProductPlan p = plan_bf16(g, epi_kind(epi));
+  if constexpr (wide_serves(Epi::kKind)) {
+    if (p.kernel == kWide) return launch_wide<AMC, BNC, SEG>(g, p, epi, s);
+  }
   if constexpr (AMC) {
     if (p.kernel == kPipe4) return launch_pipe_w<128, 2, 2, 2, AMC, BNC, SEG>(g, p, epi, s);
   } else {
@@ -1687,8 +1733,8 @@ static int splitk_plan(bool bf, int M, int N, int K, int min_k, int* kchunk) {
     sw = (K + kw - 1) / kw;
     // plus the partial tiles, written and read back at about 4 TB/s
     const int64_t sn = (K + kc - 1) / kc, part = (int64_t)M * N * 8 / 4000;
-    if (wide_time(M, (N + 255) / 256, kw / 64, sw, 0) + part * sw <
-        pipe_time(M, (N + 127) / 128, kc / 64, sn, 0) + part * sn)
+    if (wide_split_time((int64_t)t256 * sw, kw / 64) + part * sw <
+        pipe_split_time((int64_t)tiles * sn, kc / 64) + part * sn)
       kc = kw;
   }
   *kchunk = kc;

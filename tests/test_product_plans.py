@@ -13,7 +13,7 @@ import pytest
 
 # kernels (ProductKernel) and epilogues (EpiKind) of csrc/gemm.hip
 F32_32, F32_64, PIPE_32, PIPE_8, PIPE_4, WIDE = range(6)
-STORE, SCORE, GATE, HBAR, GELU, GELU_BWD, HEAD_STATS, HEAD_GRAD, PARTIAL = range(9)
+STORE, SCORE, GATE, HBAR, GELU, GELU_BWD, HEAD_STATS, HEAD_GRAD, PARTIAL, STORE_ADD, GATE_X = range(11)
 SEG_N, SEG_K = 1, 2
 
 
@@ -26,15 +26,15 @@ def plan(dtype, kind, M, N, K, amc=False, bnc=True, seg=0, seg_len=0, min_k=0):
     return out[0], tuple(out[1:4]), out[4]
 
 
-def layer_plans(B, T, D, dtype):
+def layer_plans(B, T, D, dtype, residual=False):
     """The products of a layer's forward and backward over B T rows."""
     BT = B * T
     p = {"qkv": plan(dtype, STORE, BT, 3 * D, D, seg=SEG_N, seg_len=D),
          "score": plan(dtype, SCORE, BT, D, D),
-         "gate": plan(dtype, GATE, BT, D, D),
+         "gate": plan(dtype, GATE_X if residual else GATE, BT, D, D),
          "hbar": plan(dtype, HBAR, BT, D, D, bnc=False),
          "dgrad": plan(dtype, STORE, BT, D, D, bnc=False),
-         "dx": plan(dtype, STORE, BT, D, 3 * D, bnc=False, seg=SEG_K, seg_len=D),
+         "dx": plan(dtype, STORE_ADD if residual else STORE, BT, D, 3 * D, bnc=False, seg=SEG_K, seg_len=D),
          "dWqkv": plan(dtype, PARTIAL, D, 3 * D, BT, amc=True, min_k=128),
          "dWm": plan(dtype, PARTIAL, D, D, B, amc=True, min_k=512)}
     for mk in (128, 256, 512):
@@ -47,7 +47,7 @@ def model_plans(V, d, B, T):
     BT, Vp = B * T, (V + 127) // 128 * 128
     return {"gelu": plan("bf16", GELU, BT, 4 * d, d),
             "gelu_bwd": plan("bf16", GELU_BWD, BT, 4 * d, d, bnc=False),
-            "mlp_out": plan("bf16", STORE, BT, d, 4 * d),
+            "mlp_out": plan("bf16", STORE_ADD, BT, d, 4 * d),
             "stats": plan("bf16", HEAD_STATS, BT, Vp, d, bnc=False),
             "grad": plan("bf16", HEAD_GRAD, BT, Vp, d, bnc=False)}
 
@@ -80,3 +80,34 @@ def test_every_kernel_is_reached():
     assert (p["qkv"][0], p["score"][0], p["dx"][0]) == (PIPE_8, PIPE_8, PIPE_4)
     assert all(v[0] == WIDE for k, v in layer_plans(2, 65536, 1024, "bf16").items()
                if k in ("qkv", "score", "gate", "hbar", "dgrad", "dx"))
+
+
+@pytest.mark.parametrize("M,D,residual,name,pipe_us,wide_us", [
+    (12288, 1024, False, "gate", 41.7, 53.3),
+    (24576, 1152, False, "gate", 89.2, 106.6),
+    (65536, 384, True, "dx", 85.6, 102.5),
+    (24576, 896, True, "dx", 137.3, 157.3),
+    (20000, 1152, True, "dgrad", 59.4, 66.1),
+    (24576, 1536, True, "score", 130.4, 139.0),
+    (32768, 1024, True, "dx", 224.7, 171.4),
+    (131072, 1024, True, "gate", 494.2, 456.3),
+    (16384, 1024, True, "qkv", 107.7, 92.2),
+])
+def test_measured_products_run_on_the_faster_kernel(M, D, residual, name, pipe_us, wide_us):
+    """Products of layers timed on 128 x 128 and on 256 x 256 tiles."""
+    kernel = layer_plans(1, M, D, "bf16", residual)[name][0]
+    assert (kernel == WIDE) == (wide_us < pipe_us)
+
+
+@pytest.mark.parametrize("V,d,BT,name,pipe_us,wide_us", [
+    (8000, 640, 16484, "gelu", 103.2, 144.0),
+    (8000, 640, 16484, "gelu_bwd", 108.6, 147.7),
+    (50257, 512, 16384, "gelu", 79.4, 95.4),
+    (8000, 640, 16484, "stats", 203.2, 221.7),
+    (8000, 640, 16484, "grad", 209.7, 247.0),
+    (50257, 768, 4100, "stats", 416.6, 390.7),
+    (50257, 768, 4100, "grad", 476.4, 430.4),
+])
+def test_measured_model_products_run_on_the_faster_kernel(V, d, BT, name, pipe_us, wide_us):
+    kernel = model_plans(V, d, 1, BT)[name][0]
+    assert (kernel == WIDE) == (wide_us < pipe_us)

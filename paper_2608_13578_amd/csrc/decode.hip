@@ -42,8 +42,7 @@ constexpr int kDvRowStep = 4 * kDvRowsPerWave;  // rows per round of the 4 waves
 constexpr int kDvMaxKc = 128;               // K rows per workgroup at most (4 rounds)
 constexpr int kDecMaxBatch = 64;
 
-template <typename T>
-constexpr int dv_cols() { return kDvLanesPerRow * Vec16<T>::N; }
+constexpr int kDvCols = kDvLanesPerRow * 4;  // columns of a tile
 
 // The weight as up to three column segments of width seg (Wq | Wk | Wv).
 template <typename T>
@@ -57,16 +56,16 @@ struct DvW {
   }
 };
 
-// part[ky][b][n] = sum over the rows k of split ky of x[b, k] W[k, n], for a
+// The float32 product: part[ky][b][n] = sum over the rows k of split ky of x[b, k] W[k, n], for a
 // column tile of CT columns, kc rows (a multiple of 32) and up to kDvB
 // sequences per workgroup.  Lane (column vector cg, row lane rl) of wave w
 // takes rows w*8 + rl + 32u; the row lanes meet by shuffles, the waves in
 // LDS.
-template <typename T>
-__global__ __launch_bounds__(256) void dec_gemv_part_kernel(const T* __restrict__ x, int64_t ldx,
-                                                            int B, DvW<T> w, int K, int N, int kc,
+__global__ __launch_bounds__(256) void dec_gemv_part_kernel(const float* __restrict__ x,
+                                                            int64_t ldx, int B, DvW<float> w,
+                                                            int K, int N, int kc,
                                                             float* __restrict__ part) {
-  constexpr int VE = Vec16<T>::N, CT = dv_cols<T>();
+  constexpr int VE = 4, CT = kDvCols;
   __shared__ float xs[kDvB][kDvMaxKc];
   __shared__ float red[4][kDvB][CT];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -77,13 +76,13 @@ __global__ __launch_bounds__(256) void dec_gemv_part_kernel(const T* __restrict_
   const int kn = min(kc, K - k0);
   // The weight tile's loads go out first; x (tiny) is staged meanwhile.
   const int cg = lane % kDvLanesPerRow, rl = lane / kDvLanesPerRow;
-  const T* wcol = w.col(n0 + cg * VE) + (int64_t)k0 * w.ld;
+  const float* wcol = w.col(n0 + cg * VE) + (int64_t)k0 * w.ld;
   constexpr int U = kDvMaxKc / kDvRowStep;
-  typename Vec16<T>::type wv[U];
+  f32x4 wv[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
     const int r = wave * kDvRowsPerWave + rl + u * kDvRowStep;
-    wv[u] = r < kn ? load16(wcol + (int64_t)r * w.ld) : typename Vec16<T>::type{};
+    wv[u] = r < kn ? load16(wcol + (int64_t)r * w.ld) : f32x4{};
   }
   // x[b0.., k0..k0+kc) as 16-byte vectors (kc and K are multiples of 32).
   {
@@ -91,9 +90,9 @@ __global__ __launch_bounds__(256) void dec_gemv_part_kernel(const T* __restrict_
     for (int e = tid; e < kDvB * kv; e += blockDim.x) {
       const int b = e / kv, k = (e - b * kv) * VE;
       const auto v = (b < nbt && k < kn) ? load16(x + (int64_t)(b0 + b) * ldx + k0 + k)
-                                         : typename Vec16<T>::type{};
+                                         : f32x4{};
 #pragma unroll
-      for (int q = 0; q < VE; ++q) xs[b][k + q] = to_f32(v[q]);
+      for (int q = 0; q < VE; ++q) xs[b][k + q] = v[q];
     }
   }
   __syncthreads();
@@ -110,7 +109,7 @@ __global__ __launch_bounds__(256) void dec_gemv_part_kernel(const T* __restrict_
       for (int b = 0; b < kDvB; ++b) {
         const float xb = xs[b][r];
 #pragma unroll
-        for (int e = 0; e < VE; ++e) acc[b][e] += xb * to_f32(wv[u][e]);
+        for (int e = 0; e < VE; ++e) acc[b][e] += xb * wv[u][e];
       }
     }
   }
@@ -314,19 +313,19 @@ __global__ __launch_bounds__(NW * 64) void dec_mfma_part_kernel(const bf16* __re
 // Waves (32-deep K steps) of a workgroup of the kernel above.
 constexpr int kDvWaves = 4;
 
-// h = o Wo into the block cache at slot off, and per 64 columns the part of
+// In float32, h = o Wo into the block cache at slot off, and per 64 columns the part of
 // the pooling score h . wp.  Thread = column n of sequence blockIdx.y.
-template <typename T>
 __global__ __launch_bounds__(256) void dec_wo_finish_kernel(const float* __restrict__ part, int ks,
-                                                            int B, int D, const T* __restrict__ wp,
-                                                            T* __restrict__ Hc,
+                                                            int B, int D,
+                                                            const float* __restrict__ wp,
+                                                            float* __restrict__ Hc,
                                                             float* __restrict__ spc, int L,
                                                             int off) {
   const int b = blockIdx.y, n = blockIdx.x * blockDim.x + threadIdx.x;
   const bool on = n < D;
   const float v = on ? dv_sum(part, ks, B, D, b, n) : 0.f;
-  if (on) Hc[((int64_t)b * L + off) * D + n] = from_f32<T>(v);
-  const float sc = wave_sum(on ? v * to_f32(wp[n]) : 0.f);
+  if (on) Hc[((int64_t)b * L + off) * D + n] = v;
+  const float sc = wave_sum(on ? v * wp[n] : 0.f);
   if ((threadIdx.x & 63) == 0 && on) spc[((int64_t)b * L + off) * (D / 64) + n / 64] = sc;
 }
 
@@ -560,7 +559,7 @@ int dec_splits(DType dt, int K, int N, int B) {
     return (K + kc - 1) / kc;
   }
   int kc;
-  return dv_plan(K, N, B, dv_cols<float>(), &kc);
+  return dv_plan(K, N, B, kDvCols, &kc);
 }
 
 size_t dec_part_bytes(DType dt, int B, int D) {
@@ -579,11 +578,11 @@ hipError_t dec_product(DType dt, const void* x, int64_t ldx, const void* W0, con
                        (const bf16*)x, ldx, B, w, D, N, part, DvFinish{});
   } else {
     int kc;
-    const int ks = dv_plan(D, N, B, dv_cols<float>(), &kc);
+    const int ks = dv_plan(D, N, B, kDvCols, &kc);
     const DvW<float> w{
         {(const float*)W0, (const float*)(W1 ? W1 : W0), (const float*)(W2 ? W2 : W0)}, D, D};
-    hipLaunchKernelGGL(dec_gemv_part_kernel<float>,
-                       dim3(N / dv_cols<float>(), ks, (B + kDvB - 1) / kDvB), dim3(256), 0, s,
+    hipLaunchKernelGGL(dec_gemv_part_kernel,
+                       dim3(N / kDvCols, ks, (B + kDvB - 1) / kDvB), dim3(256), 0, s,
                        (const float*)x, ldx, B, w, D, N, kc, part);
   }
   return hipGetLastError();
@@ -613,7 +612,7 @@ hipError_t dec_attn(DType dt, const float* part, int ks, void* Kc, void* Vc, voi
 
 hipError_t dec_wo_finish(const float* part, int ks, const void* wp, void* Hc, float* spc, int B,
                          int D, int L, int off, hipStream_t s) {
-  hipLaunchKernelGGL(dec_wo_finish_kernel<float>, dim3((D + 255) / 256, B), dim3(256), 0, s, part,
+  hipLaunchKernelGGL(dec_wo_finish_kernel, dim3((D + 255) / 256, B), dim3(256), 0, s, part,
                      ks, B, D, (const float*)wp, (float*)Hc, spc, L, off);
   return hipGetLastError();
 }

@@ -1884,8 +1884,9 @@ hipError_t gemm_gelu_bwd(DType dt, const GemmDesc& g, const void* U, void* dU, i
   return launch_any<bf16, false, false, kSegNone>(g, e, s);
 }
 
-// Both head products need the pipelined kernel (its epilogue layout) and
-// whole 128-column tiles.
+// Both head products need a bf16 kernel that hands an epilogue 8 columns at a
+// time, 16 consecutive lanes a row's 128 (all of them do), and whole 128-column
+// groups.
 static bool head_shape_ok(const GemmDesc& g) {
   return !g.a_mcontig && !g.b_ncontig && g.seg == kSegNone && g.splits <= 1 && g.K % 64 == 0 &&
          g.M >= 8 && g.N % 128 == 0;

@@ -188,9 +188,9 @@ __global__ __launch_bounds__(256) void pool_fwd_kernel(const T* __restrict__ H,
 // = (16-byte vector v of the row, token group tg); the block's scores are
 // formed once per workgroup (the column-chunk layout forms them once per
 // chunk) and staged in LDS with their exponentials, 1024 tokens at a time
-// with the running maximum rescaling the partial sums.  Chunks of VR
-// vectors per row and TG token groups: NT = VR * TG threads, a multiple of
-// 64 (pool_row_groups).
+// with the running maximum rescaling the partial sums.  VR vectors per row
+// and TG token groups: VR * TG threads, rounded up to whole waves (the launch
+// picks TG; threads past VR * TG only take part in the scores and barriers).
 constexpr int kRowTile = 1024;
 // Whole-row pooling needs at least this many (block, batch element) pairs;
 // fewer take the column-chunk layout, which deals each pair to several

@@ -1525,8 +1525,8 @@ template <class T>
 EpiKind epi_kind(const EpiGate<T>& e) { return e.e.X ? kEpiGateX : kEpiGate; }
 
 // Time models (ns) of a bf16 product of `slabs` 64-deep slabs in `tiles` tiles
-// on the two kernels, fitted to 1566 products of layers and 14 of heads, each timed
-// on both (D = 64 to 2048, M = 2048 to 131072).
+// on the two kernels, fitted to 1345 products of layers and heads (D = 256 to
+// 2048, M = 2048 to 131072), each timed on both.
 //   128 x 128 tiles, two per CU: rounds of 512 tiles, each 0.92 us a slab and
 //     an epilogue (EpiCost), 5 us of which the next round hides; over many
 //     rounds 0.8 us more each; a partial round costs half of a whole one and
@@ -1574,8 +1574,12 @@ int64_t wide_time(int64_t tiles, int64_t slabs, int64_t epi) {
 }
 
 // The same for the split weight gradients (two row-contiguous operands, a
-// float32 partial tile), from 40 shapes: in proportion to the 128 x 128 tiles,
-// a partial round of 256 x 256 tiles 0.85 of a whole one.
+// float32 partial tile): in proportion to the 128 x 128 tiles, a partial round
+// of 256 x 256 tiles 0.85 of a whole one.  Of 44 layer shapes (D = 256 to 1536,
+// M = 16384 to 131072) that this puts on 256 x 256 tiles, with the sum of their
+// partials, three were faster on 128 x 128 by 2 to 4 % (D = 384, M = 65536: 191
+// against 184 us), the others slower by up to 88 % (D = 1280, M = 32768: 517
+// against 969).
 int64_t pipe_split_time(int64_t tiles, int64_t slabs) { return 5000 + tiles * slabs * 1170 / 512; }
 int64_t wide_split_time(int64_t tiles, int64_t slabs) {
   const int64_t round = slabs * 1290 + 8000;
